@@ -241,6 +241,10 @@ struct alignas(16) WinRun {
   int32_t rot, has_b, b_inner, pad_;
 };
 
+// Reader counters the allocation-free adjoint keeps in its static device
+// array (4 MiB).
+constexpr int ADJ_NOALLOC_COUNTERS = 1 << 20;
+
 // Adjoint: one entry per (source cell, ghost row) contribution, sorted by
 // source cell then ghost cell.
 struct CscHost {
@@ -249,6 +253,7 @@ struct CscHost {
   std::vector<int64_t> ghost;     // ghost cell of each entry
   std::vector<double> w;          // weight of each entry
   std::vector<int32_t> rot;       // inverse rotation code of each entry
+  std::vector<int32_t> row;       // ghost row of each entry in the plan's row numbering
   // Fixed-width copy (width aw = largest entry count, at most ADJ_MAXW): the
   // entries of source k at k*aw + m, m < cnt[k], so that a source's entries
   // are addressed without reading ptr first.  Sources with cnt > aw use the
@@ -279,9 +284,6 @@ constexpr int ADJ_LDS_ROWS = 64;  // 32..160 measured: 64 is fastest at C768 x 3
 constexpr int ADJ_LDS_BLOCK = 256;  // threads of the LDS adjoint's workgroups
 constexpr int ADJ_LDS_BYTES = 40 * 1024;
 constexpr int ADJ_ZERO_ROWS = 64;  // rows per zeroing workgroup
-// Reader counters the allocation-free adjoint keeps in its static device
-// array (4 MiB).
-constexpr int ADJ_NOALLOC_COUNTERS = 1 << 20;
 struct AdjLdsTile {
   int32_t first_src, nsrc, first_u, nu;
 };
@@ -293,6 +295,47 @@ struct AdjLdsHost {
   std::vector<int32_t> u_ctr;       // counter of a row several tiles read, else -1
   std::vector<int32_t> ctr_init;    // reader tiles per counter
   std::vector<uint16_t> slot;       // per source k, entry m < cnt[k]: LDS slot, at k*aw + m
+  std::vector<int32_t> zero_rows;   // covered ghost rows that no source reads
+};
+
+// Wide adjoint (point-major plans with a source of more than ADJ_MAXW entries,
+// which the LDS adjoint's fixed-width table cannot hold, or with rows of
+// ADJW_ROW_BYTES and up).  Sources are put in the order in which the ghosts they feed are
+// visited with the thinnest box dimension innermost (for a halo strip: every
+// depth at one tangential position, then the next position), and cut greedily
+// into tiles of at most ADJW_SRC sources whose distinct ghost rows and entries
+// fit.  A workgroup takes one tile and one slice of the inner values: up to
+// ADJW_LANES lanes of one vector each.  Reader counters are kept per (shared
+// ghost row, slice).
+constexpr int ADJW_SRC = 256, ADJW_UCAP = 256, ADJW_ECAP = 1024, ADJW_LANES = 16;
+constexpr int ADJW_SPG = 4;                  // sources per row group at most
+constexpr int ADJW_ROW_BYTES = 128;          // plans of few entries per source: rows from here on
+// tiles are kept short enough for about 3 workgroups per CU: FP64 C768 x 32
+// 10.1 us with 768, 10.6 with 512, 13.9 with 1024 (two rounds of workgroups)
+constexpr int ADJW_ITEMS = 768;
+constexpr int ADJW_STAGE_BYTES = 24 * 1024;  // staged ghost slices of a tile
+struct alignas(16) AdjWTile {
+  int32_t first_src, nsrc, first_u, nu;
+  int32_t e0, ne, rp0, pad_;
+};
+struct alignas(16) AdjWGhost {
+  int32_t cell, rot, ctr, pad_;  // rot: applied to the slots read; ctr: shared-row number, or -1
+};
+struct AdjWideHost {
+  bool ok = false;
+  int32_t lanes_shift = 0;  // log2 lanes per row slice
+  int32_t nslices = 0;
+  int32_t maxu = 0, maxe = 0;       // largest nu and ne over the tiles (LDS sizing)
+  std::vector<AdjWTile> tiles;
+  std::vector<int32_t> src;         // source cells in tile order
+  std::vector<int32_t> rp;          // per tile: nsrc + 1 entry starts, relative to the tile's e0
+  std::vector<double> w;            // entries in tile order: weight
+  std::vector<int32_t> slot;        // entries in tile order: staged ghost
+  std::vector<AdjWGhost> ghosts;    // distinct ghost rows of each tile
+  std::vector<int32_t> ctr_init;    // reader tiles per (shared ghost row, slice)
+  // whether its counters fit the allocation-free adjoint's array (a plan
+  // whose counters do not keeps the other kernels' tables for that call)
+  bool alone() const { return ok && ctr_init.size() <= (size_t)ADJ_NOALLOC_COUNTERS; }
   std::vector<int32_t> zero_rows;   // covered ghost rows that no source reads
 };
 
@@ -315,6 +358,7 @@ struct HostTables {
   CscHost csc;
   std::vector<AdjTile> adj_tiles;
   AdjLdsHost adj_lds;
+  AdjWideHost adj_wide;
   // point-major row tables (device order) and tiles
   std::vector<int32_t> row_dst;  // destination cell of every covered row
   std::vector<int32_t> row_src;  // MAP rows: source cell; other rows: 0
@@ -432,6 +476,15 @@ struct Plan {
   int32_t* d_al_ctr = nullptr;  // reader counters (restored by every adjoint call)
   const uint16_t* d_al_slot = nullptr;
   const int32_t* d_al_zero = nullptr;
+  void* d_aw_dev = nullptr;  // allocation holding the wide adjoint's tables
+  const AdjWTile* d_aw_tiles = nullptr;
+  const int32_t* d_aw_src = nullptr;
+  const int32_t* d_aw_rp = nullptr;
+  const void* d_aw_ent = nullptr;  // packed {weight, slot * values per slice} per entry
+  const AdjWGhost* d_aw_ghost = nullptr;
+  const int32_t* d_aw_ctrinit = nullptr;
+  int32_t* d_aw_ctr = nullptr;  // reader counters (restored by every adjoint call)
+  const int32_t* d_aw_zero = nullptr;
   const AdjTile* d_adj_tiles = nullptr;
   // 27-point consumer: per block and neighbour direction, the block the BC
   // copies from (-1 zero rows, -2 uncovered); computed at plan creation.

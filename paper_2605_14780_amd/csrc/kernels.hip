@@ -1598,6 +1598,186 @@ __global__ __launch_bounds__(256) void k_adjoint_lds(PlanDesc d, AdjDesc a, AdjL
   }
 }
 
+// Wide adjoint (AdjWideHost): one workgroup per (tile, slice of the inner
+// values).  The tile's distinct ghost rows are staged in LDS once (this
+// slice's slots, through each row's component rotation and sign), with its
+// entries and the rows of its sources (in registers) loaded beside them, so
+// that everything a tile reads is in flight before its one barrier.  Each
+// source then sums its entries from LDS in ascending ghost order, EC entries
+// per step, from -0.0 with FMAs only: the bits of the CSR-walking kernel's
+// first product and FMAs.  A staged row read by this tile alone is zeroed by
+// it; one that several tiles read has a counter per slice, decremented after
+// the barrier (the row's loads have returned), and the last reader zeroes it
+// and restores the counter.  The decrements are in flight during the sums,
+// and the resets come after the sources' stores: resets of unshared rows
+// straight after the barrier cost 2 us (C192 x 64 quadrature 16.2 us).
+// Bound by memory after a 3 us launch: C192 x 64 FP64 quadrature rows (13
+// entries a source, 37 MB) 14 us against 77 + 6 us of the CSR-walking kernel,
+// which gathers each ghost row 13 times, and its zero pass; C384 x 256 85
+// against 399 us (3.7 TB/s).
+// Workgroups past the items zero the covered ghosts that no source reads.
+struct AdjWDesc {
+  const AdjWTile* tiles;
+  const int32_t* src;
+  const int32_t* rp;
+  const void* ent;
+  const AdjWGhost* ghost;
+  const int32_t* ctrinit;
+  int32_t* ctr;
+  const int32_t* zero;
+  int32_t ntiles, nslices, nzero, ucap, ecap;
+};
+
+template <typename T, int V, bool NT>
+__global__ __launch_bounds__(256) void k_adjoint_wide(PlanDesc d, AdjWDesc q) {
+  extern __shared__ __align__(16) unsigned char aw_smem[];
+  __shared__ int32_t zflag[ADJW_UCAP];
+  constexpr int NIT = ADJW_STAGE_BYTES / (256 * (int)sizeof(T) * V);  // staging items per thread
+  constexpr int NE = (ADJW_ECAP + 255) / 256;
+  constexpr int SPG = ADJW_SPG, EC = 4;
+  typedef T vt __attribute__((ext_vector_type(V)));
+  const int shift = d.lpr_shift, lpr = 1 << shift, S = V << shift;
+  const int inner = (int)d.inner;
+  T* __restrict__ f = static_cast<T*>(d.field);
+  const int tid = (int)threadIdx.x;
+  Pack<T, V> zero;
+#pragma unroll
+  for (int i = 0; i < V; ++i) zero.v[i] = T(0);
+  const int items = q.ntiles * q.nslices;
+  int b = (int)blockIdx.x;
+  if (b >= items) {
+    const int nvec = inner / V, r0 = (b - items) * ADJ_ZERO_ROWS, nr = min(ADJ_ZERO_ROWS, q.nzero - r0);
+    for (int e = tid; e < nr * nvec; e += 256) {
+      const int r = e / nvec, v = e - r * nvec;
+      stv<T, V, NT>(f + (int64_t)q.zero[r0 + r] * d.cs + (int64_t)v * V, zero);
+    }
+    return;
+  }
+  {  // a contiguous range of items per XCD (neighbouring tiles share ghost rows and source lines)
+    const int nq = items >> 3, rem = items & 7, x = b & 7, jx = b >> 3;
+    b = x * nq + min(x, rem) + jx;
+  }
+  const int ti = b / q.nslices, s = b - ti * q.nslices;
+  const AdjWTile tl = q.tiles[ti];
+  T* lds = reinterpret_cast<T*>(aw_smem);                                             // ucap x S values
+  WideEnt<T>* le = reinterpret_cast<WideEnt<T>*>(aw_smem + (size_t)q.ucap * S * sizeof(T));  // ecap entries
+  int32_t* lp = reinterpret_cast<int32_t*>(le + q.ecap);                              // nsrc + 1 entry starts
+  const int lane = tid & (lpr - 1), grp = tid >> shift, ngrp = 256 >> shift;
+  const int l = s * S + lane * V;
+  const bool in = l < inner;
+  // the tile's ghosts and sources, then its entries, then the rows themselves
+  int32_t gcell[NIT], grot[NIT];
+#pragma unroll
+  for (int k = 0; k < NIT; ++k) {
+    const int u = grp + k * ngrp;  // item tid + 256 k: ghost u, this thread's lane
+    gcell[k] = -1;
+    if (u < tl.nu) {
+      const AdjWGhost g = q.ghost[tl.first_u + u];
+      gcell[k] = g.cell;
+      grot[k] = g.rot;
+    }
+  }
+  int32_t scell[SPG];
+#pragma unroll
+  for (int k = 0; k < SPG; ++k) scell[k] = grp + k * ngrp < tl.nsrc ? q.src[tl.first_src + grp + k * ngrp] : -1;
+  typedef uint32_t eu __attribute__((ext_vector_type(sizeof(WideEnt<T>) / 4)));
+  const eu* __restrict__ gent = reinterpret_cast<const eu*>(q.ent) + tl.e0;
+  eu ev[NE];
+#pragma unroll
+  for (int k = 0; k < NE; ++k)
+    if (tid + k * 256 < tl.ne) ev[k] = gent[tid + k * 256];
+  int32_t rp0 = 0, rp1 = 0;  // nsrc + 1 <= 257 starts
+  if (tid <= tl.nsrc) rp0 = q.rp[tl.rp0 + tid];
+  if (tid == 0 && tl.nsrc == 256) rp1 = q.rp[tl.rp0 + 256];
+  Pack<T, V> g[NIT];
+  T gs[NIT];
+#pragma unroll
+  for (int k = 0; k < NIT; ++k)
+    if (gcell[k] >= 0 && in) {
+      const int64_t sl = rot_slot<T>(d, grot[k], l, gs[k]);
+      g[k] = ldv<T, V>(f + (int64_t)gcell[k] * d.cs + sl);
+    }
+  Pack<T, V> x[SPG];
+#pragma unroll
+  for (int k = 0; k < SPG; ++k)
+    if (scell[k] >= 0 && in) x[k] = ldv<T, V>(f + (int64_t)scell[k] * d.cs + l);
+#pragma unroll
+  for (int k = 0; k < NE; ++k)
+    if (tid + k * 256 < tl.ne) reinterpret_cast<eu*>(le)[tid + k * 256] = ev[k];
+  if (tid <= tl.nsrc) lp[tid] = rp0;
+  if (tid == 0 && tl.nsrc == 256) lp[256] = rp1;
+#pragma unroll
+  for (int k = 0; k < NIT; ++k)
+    if (gcell[k] >= 0 && in) {
+      vt w;
+#pragma unroll
+      for (int i = 0; i < V; ++i) w[i] = gs[k] * g[k].v[i];
+      *reinterpret_cast<vt*>(&lds[(tid + k * 256) * V]) = w;
+    }
+  __syncthreads();  // every load of this tile's ghost rows has returned
+  int z = 0, c = -1;
+  if (tid < tl.nu) {
+    c = q.ghost[tl.first_u + tid].ctr;
+    z = c < 0 ? 1 : (atomicSub(&q.ctr[(int64_t)c * q.nslices + s], 1) == 1 ? 1 : 0);
+  }
+  if (in) {
+    const T* __restrict__ xl = lds + lane * V;
+#pragma unroll
+    for (int k = 0; k < SPG; ++k) {
+      const int r = grp + k * ngrp;
+      if (r >= tl.nsrc) break;
+      const int e0 = lp[r], e1 = lp[r + 1];
+      vt y;
+#pragma unroll
+      for (int i = 0; i < V; ++i) y[i] = T(-0.0);
+      int e = e0;
+      for (; e + EC <= e1; e += EC) {
+        T w[EC];
+        int o[EC];
+#pragma unroll
+        for (int m = 0; m < EC; ++m) ld_ent<T>(le + e + m, w[m], o[m]);
+        vt v[EC];
+#pragma unroll
+        for (int m = 0; m < EC; ++m) v[m] = *reinterpret_cast<const vt*>(xl + o[m]);
+#pragma unroll
+        for (int m = 0; m < EC; ++m)
+#pragma unroll
+          for (int i = 0; i < V; ++i) y[i] = fma(w[m], v[m][i], y[i]);
+      }
+      if (e < e1) {  // the last 1..EC-1 entries: clamped reads, dead steps dropped by a select
+        T w[EC - 1];
+        int o[EC - 1];
+#pragma unroll
+        for (int m = 0; m < EC - 1; ++m) ld_ent<T>(le + min(e + m, e1 - 1), w[m], o[m]);
+        vt v[EC - 1];
+#pragma unroll
+        for (int m = 0; m < EC - 1; ++m) v[m] = *reinterpret_cast<const vt*>(xl + o[m]);
+#pragma unroll
+        for (int m = 0; m < EC - 1; ++m) {
+          const bool lv = e + m < e1;
+#pragma unroll
+          for (int i = 0; i < V; ++i) y[i] = lv ? fma(w[m], v[m][i], y[i]) : y[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < V; ++i) x[k].v[i] = x[k].v[i] + y[i];
+      stv<T, V, NT>(f + (int64_t)scell[k] * d.cs + l, x[k]);
+    }
+  }
+  if (tid < tl.nu) {
+    if (z && c >= 0) atomicExch(&q.ctr[(int64_t)c * q.nslices + s], q.ctrinit[(int64_t)c * q.nslices + s]);
+    zflag[tid] = z;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NIT; ++k)
+    if (gcell[k] >= 0 && in && zflag[grp + k * ngrp]) {
+      T sign;
+      const int64_t sl = rot_slot<T>(d, grot[k], l, sign);
+      stv<T, V, NT>(f + (int64_t)gcell[k] * d.cs + sl, zero);
+    }
+}
+
 // ---- 27-point consumer on Cartesian blocks with a one-cell halo ----------------------------
 struct StDesc {
   int32_t nblk, nz, ny, nx;
@@ -2154,15 +2334,15 @@ struct Packer {
   }
   // wide-row entries as WideEnt<T>: the weight in the plan's type (rounded as
   // in reals) and the LDS offset of the source cell's slice (slot * values
-  // per slice of sb bytes)
-  size_t wide_entries(const std::vector<double>& w, const std::vector<int32_t>& slot, int dtype, int sb) {
+  // per slice)
+  size_t wide_entries(const std::vector<double>& w, const std::vector<int32_t>& slot, int dtype, int values) {
     if (dtype == HBC_F64) {
       std::vector<WideEnt<double>> e(w.size());
-      for (size_t k = 0; k < w.size(); ++k) e[k] = {w[k], slot[k] * (sb / 8)};
+      for (size_t k = 0; k < w.size(); ++k) e[k] = {w[k], slot[k] * values};
       return vec(e);
     }
     std::vector<WideEnt<float>> e(w.size());
-    for (size_t k = 0; k < w.size(); ++k) e[k] = {(float)w[k], slot[k] * (sb / 4)};
+    for (size_t k = 0; k < w.size(); ++k) e[k] = {(float)w[k], slot[k] * values};
     return vec(e);
   }
 };
@@ -2229,6 +2409,8 @@ void device_free_plan(Plan& p) {
   p.d_csc_dev = nullptr;
   if (p.d_al_dev) (void)hipFree(p.d_al_dev);
   p.d_al_dev = nullptr;
+  if (p.d_aw_dev) (void)hipFree(p.d_aw_dev);
+  p.d_aw_dev = nullptr;
   if (p.d_dr_scratch) (void)hipFree(p.d_dr_scratch);
   p.d_dr_scratch = nullptr;
   p.d_csc_src = nullptr;
@@ -2252,7 +2434,7 @@ void device_upload_plan(Plan& p) {
   size_t o_wu = pk.vec(T.w_ucell);
   size_t o_wr = pk.vec(T.w_row);
   size_t o_wp = pk.vec(T.w_rp);
-  size_t o_we = pk.wide_entries(T.w_entw, T.w_ents, p.dtype, wide_slice_bytes(p));
+  size_t o_we = pk.wide_entries(T.w_entw, T.w_ents, p.dtype, wide_slice_bytes(p) / (p.dtype == HBC_F64 ? 8 : 4));
   size_t o_nt = pk.vec(T.ntiles);
   size_t o_drc = pk.vec(T.dr_cell);
   size_t o_drp = pk.vec(T.dr_ptr);
@@ -2339,31 +2521,33 @@ void device_upload_tiles(Plan& p) {
 }
 
 void device_upload_csc(Plan& p) {
-  Packer pk;
-  const CscHost& C = p.host.csc;
-  size_t o_src = pk.vec(C.src_cell);
-  size_t o_ptr = pk.vec(C.ptr);
-  size_t o_gh = pk.vec(C.ghost);
-  size_t o_w = pk.reals(C.w, p.dtype);
-  size_t o_rot = pk.vec(C.rot);
-  size_t o_cnt = pk.vec(C.cnt);
-  size_t o_fg = pk.vec(C.fghost);
-  size_t o_fw = pk.reals(C.fw, p.dtype);
-  size_t o_frot = pk.vec(C.frot);
-  void* dev = nullptr;
-  HIP_CHECK(hipMalloc(&dev, pk.buf.size()));
-  p.d_csc_dev = dev;
-  HIP_CHECK(hipMemcpy(dev, pk.buf.data(), pk.buf.size(), hipMemcpyHostToDevice));
-  char* b = static_cast<char*>(dev);
-  p.d_csc_src = reinterpret_cast<const int64_t*>(b + o_src);
-  p.d_csc_ptr = reinterpret_cast<const int64_t*>(b + o_ptr);
-  p.d_csc_ghost = reinterpret_cast<const int64_t*>(b + o_gh);
-  p.d_csc_w = b + o_w;
-  p.d_csc_rot = reinterpret_cast<const int32_t*>(b + o_rot);
-  p.d_adj_cnt = reinterpret_cast<const int32_t*>(b + o_cnt);
-  p.d_adj_fg = reinterpret_cast<const int32_t*>(b + o_fg);
-  p.d_adj_fw = b + o_fw;
-  p.d_adj_frot = reinterpret_cast<const int8_t*>(b + o_frot);
+  if (!p.host.adj_wide.alone()) {
+    Packer pk;
+    const CscHost& C = p.host.csc;
+    size_t o_src = pk.vec(C.src_cell);
+    size_t o_ptr = pk.vec(C.ptr);
+    size_t o_gh = pk.vec(C.ghost);
+    size_t o_w = pk.reals(C.w, p.dtype);
+    size_t o_rot = pk.vec(C.rot);
+    size_t o_cnt = pk.vec(C.cnt);
+    size_t o_fg = pk.vec(C.fghost);
+    size_t o_fw = pk.reals(C.fw, p.dtype);
+    size_t o_frot = pk.vec(C.frot);
+    void* dev = nullptr;
+    HIP_CHECK(hipMalloc(&dev, pk.buf.size()));
+    p.d_csc_dev = dev;
+    HIP_CHECK(hipMemcpy(dev, pk.buf.data(), pk.buf.size(), hipMemcpyHostToDevice));
+    char* b = static_cast<char*>(dev);
+    p.d_csc_src = reinterpret_cast<const int64_t*>(b + o_src);
+    p.d_csc_ptr = reinterpret_cast<const int64_t*>(b + o_ptr);
+    p.d_csc_ghost = reinterpret_cast<const int64_t*>(b + o_gh);
+    p.d_csc_w = b + o_w;
+    p.d_csc_rot = reinterpret_cast<const int32_t*>(b + o_rot);
+    p.d_adj_cnt = reinterpret_cast<const int32_t*>(b + o_cnt);
+    p.d_adj_fg = reinterpret_cast<const int32_t*>(b + o_fg);
+    p.d_adj_fw = b + o_fw;
+    p.d_adj_frot = reinterpret_cast<const int8_t*>(b + o_frot);
+  }
   const AdjLdsHost& A = p.host.adj_lds;
   if (A.ok) {
     Packer q;
@@ -2386,6 +2570,31 @@ void device_upload_csc(Plan& p) {
     p.d_al_ctr = reinterpret_cast<int32_t*>(c + o_ct);
     p.d_al_slot = reinterpret_cast<const uint16_t*>(c + o_sl);
     p.d_al_zero = reinterpret_cast<const int32_t*>(c + o_z);
+  }
+  const AdjWideHost& W = p.host.adj_wide;
+  if (W.ok) {
+    Packer q;
+    size_t o_t = q.vec(W.tiles);
+    size_t o_s = q.vec(W.src);
+    size_t o_rp = q.vec(W.rp);
+    size_t o_e = q.wide_entries(W.w, W.slot, p.dtype, p.vec << W.lanes_shift);
+    size_t o_g = q.vec(W.ghosts);
+    size_t o_ci = q.vec(W.ctr_init);
+    size_t o_ct = q.vec(W.ctr_init);  // counters start at their reader counts
+    size_t o_z = q.vec(W.zero_rows);
+    void* dv = nullptr;
+    HIP_CHECK(hipMalloc(&dv, q.buf.size()));
+    p.d_aw_dev = dv;
+    HIP_CHECK(hipMemcpy(dv, q.buf.data(), q.buf.size(), hipMemcpyHostToDevice));
+    char* c = static_cast<char*>(dv);
+    p.d_aw_tiles = reinterpret_cast<const AdjWTile*>(c + o_t);
+    p.d_aw_src = reinterpret_cast<const int32_t*>(c + o_s);
+    p.d_aw_rp = reinterpret_cast<const int32_t*>(c + o_rp);
+    p.d_aw_ent = c + o_e;
+    p.d_aw_ghost = reinterpret_cast<const AdjWGhost*>(c + o_g);
+    p.d_aw_ctrinit = reinterpret_cast<const int32_t*>(c + o_ci);
+    p.d_aw_ctr = reinterpret_cast<int32_t*>(c + o_ct);
+    p.d_aw_zero = reinterpret_cast<const int32_t*>(c + o_z);
   }
   void* t = nullptr;
   size_t nt = std::max<size_t>(1, p.host.adj_tiles.size());
@@ -2722,18 +2931,50 @@ __global__ __launch_bounds__(256) void k_copy_i32(int32_t* __restrict__ dst, con
   for (int i = blockIdx.x * 256 + (int)threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = src[i];
 }
 
+template <typename T, int V>
+static void launch_adjoint_wide(const Plan& p, const PlanDesc& d0, hipStream_t st, int32_t* ctr) {
+  const AdjWideHost& A = p.host.adj_wide;
+  PlanDesc d = d0;
+  d.lpr_shift = A.lanes_shift;
+  const int64_t items = (int64_t)A.tiles.size() * A.nslices;
+  const int64_t grid = items + ((int64_t)A.zero_rows.size() + ADJ_ZERO_ROWS - 1) / ADJ_ZERO_ROWS;
+  if (grid == 0) return;
+  if (grid >= (int64_t(1) << 31)) fail(HBC_EUNSUPPORTED, "grid too large for the wide adjoint");
+  // whole 16 bytes of staged values and of entries, so that what follows each is aligned
+  const int ucap = (A.maxu + 3) & ~3, ecap = (A.maxe + 1) & ~1;
+  AdjWDesc q{p.d_aw_tiles, p.d_aw_src, p.d_aw_rp, p.d_aw_ent, p.d_aw_ghost, p.d_aw_ctrinit, ctr ? ctr : p.d_aw_ctr,
+             p.d_aw_zero, (int32_t)A.tiles.size(), A.nslices, (int32_t)A.zero_rows.size(), ucap, ecap};
+  const size_t lds = (size_t)ucap * (V << A.lanes_shift) * sizeof(T) + (size_t)ecap * sizeof(WideEnt<T>) +
+                     (ADJW_SRC + 1) * sizeof(int32_t);
+  if (d.nt)
+    HBC_LAUNCH((k_adjoint_wide<T, V, true>), dim3((unsigned)grid), dim3(256), lds, st, d, q);
+  else
+    HBC_LAUNCH((k_adjoint_wide<T, V, false>), dim3((unsigned)grid), dim3(256), lds, st, d, q);
+  HIP_CHECK(hipGetLastError());
+}
+
 // ctr: the reader counters to use (the plan's own, or the static scratch).
 template <typename T>
-static void launch_adjoint_t(const Plan& p, const PlanDesc& d, hipStream_t st, int32_t* ctr = nullptr) {
+static void launch_adjoint_t(const Plan& p, const PlanDesc& d, hipStream_t st, int32_t* ctr = nullptr,
+                             bool wide = true) {
   AdjDesc a{p.d_csc_src, p.d_csc_ptr,  p.d_csc_ghost, p.d_csc_w,          p.d_csc_rot,
             p.d_adj_cnt, p.d_adj_fg, p.d_adj_fw,    p.d_adj_frot, p.host.csc.aw};
-  if (p.host.adj_lds.ok && p.layout.order == HBC_POINT_MAJOR) {
+  if (!(p.host.adj_wide.ok && wide) && p.host.adj_lds.ok && p.layout.order == HBC_POINT_MAJOR) {
     if (sizeof(T) == 4 && p.vec == 4)
       launch_adjoint_lds<T, (sizeof(T) == 4 ? 4 : 2)>(p, d, a, st, ctr);
     else if (p.vec >= 2)
       launch_adjoint_lds<T, 2>(p, d, a, st, ctr);
     else
       launch_adjoint_lds<T, 1>(p, d, a, st, ctr);
+    return;
+  }
+  if (p.host.adj_wide.ok && wide) {
+    if (sizeof(T) == 4 && p.vec == 4)
+      launch_adjoint_wide<T, (sizeof(T) == 4 ? 4 : 2)>(p, d, st, ctr);
+    else if (p.vec >= 2)
+      launch_adjoint_wide<T, 2>(p, d, st, ctr);
+    else
+      launch_adjoint_wide<T, 1>(p, d, st, ctr);
     return;
   }
   const int nt = (int)p.host.adj_tiles.size();
@@ -2794,8 +3035,13 @@ std::vector<std::string> device_kernel_names(const Plan& p, int op) {
 void device_adjoint_noalloc(const Plan& p, void* grad, void* stream) {
   PlanDesc d = make_desc(p, grad);
   int32_t* ctr = nullptr;
-  if (p.host.adj_lds.ok && p.layout.order == HBC_POINT_MAJOR) {
-    const size_t n = p.host.adj_lds.ctr_init.size();
+  // a wide adjoint whose (row, slice) counters exceed the static array: the
+  // LDS adjoint where the plan fits it, else the CSR-walking kernel, which
+  // needs no counters
+  const bool wide = p.host.adj_wide.alone();
+  if (wide || (p.host.adj_lds.ok && p.layout.order == HBC_POINT_MAJOR)) {
+    const size_t n = wide ? p.host.adj_wide.ctr_init.size() : p.host.adj_lds.ctr_init.size();
+    const int32_t* init = wide ? p.d_aw_ctrinit : p.d_al_ctrinit;
     if (n > (size_t)ADJ_NOALLOC_COUNTERS)
       fail(HBC_EINVAL, "the plan needs " + std::to_string(n) + " reader counters; the allocation-free adjoint holds " +
                            std::to_string(ADJ_NOALLOC_COUNTERS));
@@ -2804,14 +3050,14 @@ void device_adjoint_noalloc(const Plan& p, void* grad, void* stream) {
       // the array keeps whatever the last call on this GPU left: start every
       // counter at its reader count (a copy kernel, so the call can be captured)
       const int grid = (int)std::min<size_t>((n + 255) / 256, 1024);
-      hipLaunchKernelGGL(k_copy_i32, dim3(grid), dim3(256), 0, S(stream), ctr, p.d_al_ctrinit, (int)n);
+      hipLaunchKernelGGL(k_copy_i32, dim3(grid), dim3(256), 0, S(stream), ctr, init, (int)n);
       HIP_CHECK(hipGetLastError());
     }
   }
   if (p.dtype == HBC_F64)
-    launch_adjoint_t<double>(p, d, S(stream), ctr);
+    launch_adjoint_t<double>(p, d, S(stream), ctr, wide);
   else
-    launch_adjoint_t<float>(p, d, S(stream), ctr);
+    launch_adjoint_t<float>(p, d, S(stream), ctr, wide);
 }
 
 void device_stencil27(Plan& p, const void* x, void* y, void* stream, bool fused, void* xghost) {

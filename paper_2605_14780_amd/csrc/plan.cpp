@@ -1139,12 +1139,133 @@ static void build_adj_lds(Plan& plan) {
   A.ok = true;
 }
 
+// Tiles of the wide adjoint (see AdjWideHost).  Every source's sum keeps its
+// entries in ascending ghost order, so the order of the sources does not
+// change a bit of the result.
+static void build_adj_wide(Plan& plan, int64_t maxc) {
+  const CscHost& C = plan.host.csc;
+  const HostTables& T = plan.host;
+  AdjWideHost& A = plan.host.adj_wide;
+  A = AdjWideHost{};
+  const Layout& L = plan.layout;
+  if (L.order != HBC_POINT_MAJOR || L.inner > (int64_t(1) << 30)) return;
+  const int64_t es = plan.dtype == HBC_F64 ? 8 : 4;
+  if (maxc <= ADJ_MAXW && L.inner * es < ADJW_ROW_BYTES) return;
+  const int64_t nvec = L.inner / plan.vec;
+  while ((1 << A.lanes_shift) < std::min<int64_t>(nvec, ADJW_LANES)) ++A.lanes_shift;
+  const int64_t lanes = int64_t(1) << A.lanes_shift, slice = lanes * plan.vec;
+  A.nslices = (int32_t)((L.inner + slice - 1) / slice);
+  const int64_t ucap = std::min<int64_t>(ADJW_UCAP, ADJW_STAGE_BYTES / (slice * es));
+  const int64_t nsrc = (int64_t)C.src_cell.size(), groups = 256 / lanes;
+  const int64_t scap = std::min<int64_t>(
+      ADJW_SRC, std::max(groups, std::min(ADJW_SPG * groups, nsrc * A.nslices / ADJW_ITEMS)));
+  // visiting rank of every covered ghost row
+  const size_t nrows = T.row_dst.size();
+  std::vector<int32_t> rank(nrows, 0);
+  int32_t next = 0;
+  for (const DevSeg& sg : T.segs)
+    for (int64_t r : wide_row_order(sg)) rank[(size_t)(sg.row_base + r)] = next++;
+  std::vector<std::pair<int32_t, int32_t>> order((size_t)nsrc);  // (first rank the source feeds, source)
+  for (int64_t k = 0; k < nsrc; ++k) {
+    int32_t first = INT32_MAX;
+    for (int64_t e = C.ptr[k]; e < C.ptr[k + 1]; ++e) first = std::min(first, rank[(size_t)C.row[e]]);
+    order[(size_t)k] = {first, (int32_t)k};
+  }
+  std::sort(order.begin(), order.end());
+  std::vector<int32_t> local(nrows, -1);   // staged slot of a ghost row in the open tile
+  std::vector<int32_t> readers(nrows, 0);  // tiles that stage a ghost row
+  std::vector<int32_t> fresh, staged;      // entries with new ghost rows; the row of every staged ghost
+  size_t n = 0;
+  while (n < order.size()) {
+    AdjWTile t{};
+    t.first_src = (int32_t)A.src.size();
+    t.first_u = (int32_t)A.ghosts.size();
+    t.e0 = (int32_t)A.w.size();
+    t.rp0 = (int32_t)A.rp.size();
+    A.rp.push_back(0);
+    while (n < order.size() && t.nsrc < scap) {
+      const int64_t k = order[n].second, b = C.ptr[k], e = C.ptr[k + 1];
+      fresh.clear();
+      for (int64_t q = b; q < e; ++q)
+        if (local[(size_t)C.row[q]] < 0) {
+          local[(size_t)C.row[q]] = t.nu + (int32_t)fresh.size();
+          fresh.push_back((int32_t)q);
+        }
+      if (t.nu + (int64_t)fresh.size() > ucap || t.ne + (e - b) > ADJW_ECAP) {
+        for (int32_t q : fresh) local[(size_t)C.row[q]] = -1;
+        break;
+      }
+      for (int32_t q : fresh) {
+        A.ghosts.push_back(AdjWGhost{(int32_t)C.ghost[q], C.rot[q], -1, 0});
+        staged.push_back(C.row[q]);
+      }
+      t.nu += (int32_t)fresh.size();
+      for (int64_t q = b; q < e; ++q) {
+        A.w.push_back(C.w[q]);
+        A.slot.push_back(local[(size_t)C.row[q]]);
+      }
+      t.ne += (int32_t)(e - b);
+      A.src.push_back((int32_t)C.src_cell[k]);
+      A.rp.push_back(t.ne);
+      ++t.nsrc;
+      ++n;
+    }
+    if (t.nsrc == 0) {  // one source alone is too wide: the CSR-walking kernel serves the plan
+      A = AdjWideHost{};
+      return;
+    }
+    for (int32_t u = 0; u < t.nu; ++u) {
+      const size_t r = (size_t)staged[(size_t)(t.first_u + u)];
+      local[r] = -1;
+      ++readers[r];
+    }
+    A.maxu = std::max(A.maxu, t.nu);
+    A.maxe = std::max(A.maxe, t.ne);
+    A.tiles.push_back(t);
+  }
+  int32_t nctr = 0;
+  std::vector<int32_t>& ctr_of = local;  // all -1 again
+  for (size_t u = 0; u < staged.size(); ++u) {
+    const size_t r = (size_t)staged[u];
+    if (readers[r] < 2) continue;
+    if (ctr_of[r] < 0) {
+      ctr_of[r] = nctr++;
+      A.ctr_init.insert(A.ctr_init.end(), (size_t)A.nslices, readers[r]);
+    }
+    A.ghosts[u].ctr = ctr_of[r];
+  }
+  for (size_t r = 0; r < nrows; ++r)
+    if (readers[r] == 0) A.zero_rows.push_back(T.row_dst[r]);
+  A.ok = true;
+}
+
+// Positions of the entries by (src, ghost) cell, table order within equal
+// pairs: a radix sort over the bits the cell numbers have.
+template <typename E>
+static std::vector<uint32_t> sorted_by_cells(const std::vector<E>& ents, int64_t ncells) {
+  constexpr int B = 11;
+  int bits = 1;
+  while ((int64_t(1) << bits) < ncells) ++bits;
+  std::vector<uint32_t> order(ents.size()), next(ents.size());
+  for (size_t k = 0; k < ents.size(); ++k) order[k] = (uint32_t)k;
+  for (int key = 0; key < 2; ++key)  // ghost first, then source: every pass keeps the order of the last
+    for (int sh = 0; sh < bits; sh += B) {
+      auto digit = [&](uint32_t k) { return ((key == 0 ? ents[k].ghost : ents[k].src) >> sh) & ((1 << B) - 1); };
+      std::vector<uint32_t> at((1 << B) + 1, 0);
+      for (uint32_t k : order) ++at[(size_t)digit(k) + 1];
+      for (size_t d = 0; d < (1 << B); ++d) at[d + 1] += at[d];
+      for (uint32_t k : order) next[at[(size_t)digit(k)]++] = k;
+      order.swap(next);
+    }
+  return order;
+}
+
 void build_csc(Plan& plan) {
   const HostTables& T = plan.host;
   struct E {
     int64_t src, ghost;
     double w;
-    int32_t rot;
+    int32_t rot, row;
   };
   std::vector<E> ents;
   ents.reserve((size_t)plan.stats.nnz);
@@ -1152,6 +1273,7 @@ void build_csc(Plan& plan) {
     const int irot = rot_inverse(s.rot);
     int64_t c[SEG_MAXD];
     for (int64_t r = 0; r < s.nrows; ++r) {
+      const int32_t row = (int32_t)(s.row_base + r);
       int64_t q = r;
       for (int d = s.nd - 1; d >= 0; --d) {
         c[d] = q % s.ext[d];
@@ -1163,31 +1285,35 @@ void build_csc(Plan& plan) {
         src += c[d] * s.src_stride[d];
       }
       if (s.kind == SEG_MAP) {
-        ents.push_back(E{src, dst, s.w, irot});
+        ents.push_back(E{src, dst, s.w, irot, row});
       } else if (s.kind == SEG_ELL) {
         for (int m = 0; m < s.width; ++m) {
           int32_t col = T.ell_col[s.tab + r * s.width + m];
-          if (col >= 0) ents.push_back(E{col, dst, T.ell_val[s.tab + r * s.width + m], irot});
+          if (col >= 0) ents.push_back(E{col, dst, T.ell_val[s.tab + r * s.width + m], irot, row});
         }
       } else if (s.kind == SEG_CSR) {
         for (int64_t k = T.csr_ptr[s.tab + r]; k < T.csr_ptr[s.tab + r + 1]; ++k)
-          ents.push_back(E{T.csr_col[k], dst, T.csr_val[k], irot});
+          ents.push_back(E{T.csr_col[k], dst, T.csr_val[k], irot, row});
       }
     }
   }
-  std::sort(ents.begin(), ents.end(), [](const E& a, const E& b) {
-    return a.src != b.src ? a.src < b.src : a.ghost < b.ghost;
-  });
+  const std::vector<uint32_t> order = sorted_by_cells(ents, plan.grid.ncells);
   CscHost& C = plan.host.csc;
   C = CscHost{};
+  C.ghost.reserve(ents.size());
+  C.w.reserve(ents.size());
+  C.rot.reserve(ents.size());
+  C.row.reserve(ents.size());
   for (size_t k = 0; k < ents.size(); ++k) {
-    if (k == 0 || ents[k].src != ents[k - 1].src) {
-      C.src_cell.push_back(ents[k].src);
+    const E& e = ents[order[k]];
+    if (k == 0 || e.src != ents[order[k - 1]].src) {
+      C.src_cell.push_back(e.src);
       C.ptr.push_back((int64_t)k);
     }
-    C.ghost.push_back(ents[k].ghost);
-    C.w.push_back(ents[k].w);
-    C.rot.push_back(ents[k].rot);
+    C.ghost.push_back(e.ghost);
+    C.w.push_back(e.w);
+    C.rot.push_back(e.rot);
+    C.row.push_back(e.row);
   }
   C.ptr.push_back((int64_t)ents.size());
   const int64_t nsrc = (int64_t)C.src_cell.size();
@@ -1195,13 +1321,16 @@ void build_csc(Plan& plan) {
   for (int64_t k = 0; k < nsrc; ++k) maxc = std::max(maxc, C.ptr[k + 1] - C.ptr[k]);
   C.aw = (int32_t)std::max<int64_t>(1, std::min<int64_t>(maxc, ADJ_MAXW));
   C.cnt.assign(nsrc, 0);
+  for (int64_t k = 0; k < nsrc; ++k) C.cnt[k] = (int32_t)(C.ptr[k + 1] - C.ptr[k]);
+  build_adj_wide(plan, maxc);
+  plan.host.adj_lds = AdjLdsHost{};
+  plan.host.adj_tiles.clear();
+  if (plan.host.adj_wide.alone()) return;  // no call needs the tables below
   C.fghost.assign(nsrc * C.aw, 0);
   C.fw.assign(nsrc * C.aw, 0.0);
   C.frot.assign(nsrc * C.aw, 0);
   for (int64_t k = 0; k < nsrc; ++k) {
-    const int64_t n = C.ptr[k + 1] - C.ptr[k];
-    C.cnt[k] = (int32_t)n;
-    for (int64_t m = 0; m < std::min<int64_t>(n, C.aw); ++m) {
+    for (int64_t m = 0; m < std::min<int64_t>(C.cnt[k], C.aw); ++m) {
       const int64_t e = C.ptr[k] + m;
       C.fghost[k * C.aw + m] = (int32_t)C.ghost[e];
       C.fw[k * C.aw + m] = C.w[e];
@@ -1211,7 +1340,6 @@ void build_csc(Plan& plan) {
   build_adj_lds(plan);
   // adjoint tiles: sources grouped so that a tile holds about as many inner
   // values as a forward tile
-  plan.host.adj_tiles.clear();
   const int64_t ns = (int64_t)C.src_cell.size();
   int64_t per = std::max<int64_t>(plan.tune.block / plan.tune.lanes_per_row, ns / 2048);
   per = std::min<int64_t>(per, 16384);

@@ -228,3 +228,36 @@ def test_wide_and_narrow_kernels_under_graph_replays(I, dtype):
                 for b in bufs:
                     assert torch.equal(b, ref), (op, rep)
             del graph
+
+
+@pytest.mark.parametrize("N,h,I,dtype", [(5, 1, 1, "f64"), (9, 2, 15, "f64"), (9, 2, 32, "f64"), (8, 3, 34, "f64"),
+                                         (8, 2, 66, "f64"), (12, 3, 3, "f32"), (9, 2, 64, "f32"), (8, 2, 132, "f32")])
+def test_wide_adjoint_matches_oracle_vjp(N, h, I, dtype):
+    """Sources of more than 8 entries, at the edges of the staged slices (16
+    lanes of one vector): one value, a slice less one, a whole slice, a slice
+    and a remainder; twice, so that every reader counter was restored, and
+    without allocation."""
+    from oracle import vjp as o_vjp
+    prog = hb.Program(hb.Grid.cubed_sphere(N, h))
+    prog.cs_add_quadrature(N, h, 2)
+    plan = hb.Plan(prog, inner=I, dtype=hb.F64 if dtype == "f64" else hb.F32)
+    og = ocs.grid(N, h)
+    op = assemble(og, oq.subs(N, h, 2))
+    # a source sums up to n entries of |w| by FMAs: n + 1 roundings of at most
+    # the sum of |w| plus the data value's own
+    A = abs(next(iter(op.parts.values())))
+    n = int(A.getnnz(axis=0).max())
+    tdt, eps = (torch.float64, 2.0 ** -53) if dtype == "f64" else (torch.float32, 2.0 ** -24)
+    # FP32 weights are rounded once more; the library's FP64 weights differ from the oracle's by up to 1e-13
+    tol = (n + 2) * eps * (1 + float(A.sum(axis=0).max())) + n * 1e-13
+    for seed in (1, 2):
+        ybar = np.random.default_rng(seed).uniform(-1, 1, (og.ncells, I)).astype(np.float32).astype(np.float64)
+        ref = o_vjp(op, ybar, None)
+        for call in (hb.apply_adjoint, hb.apply_adjoint_noalloc):
+            t = torch.from_numpy(ybar).to(tdt).cuda()
+            call(plan, t)
+            torch.cuda.synchronize()
+            got = t.cpu().numpy().astype(np.float64)
+            assert (got[og.ghost_cells] == 0).all()
+            assert np.abs(got - ref).max() <= tol
+    assert any("k_adjoint_wide" in k for k in plan.kernels(hb.OP_ADJOINT))
