@@ -143,8 +143,10 @@ typedef struct {
 } hbc_stats;
 
 /* Launch shape of the apply kernels (chosen by the plan, changed by tuning).
- * The point-major adjoint's LDS kernel has a fixed shape of its own (256
- * threads, about 4 lanes per row); the other adjoint kernels follow this one. */
+ * The staged point-major adjoints and the plane-major adjoint have fixed shapes
+ * of their own; the point-major CSR-walking adjoint follows this one.
+ * Plane-major plans take one row per lane: lanes_per_row does not apply, and
+ * rows_per_tile only to rows of more than four entries. */
 typedef struct {
   int32_t block;            /* threads per workgroup: 64, 128, 192 or 256 */
   int32_t lanes_per_row;    /* power of two; lanes that share one row */

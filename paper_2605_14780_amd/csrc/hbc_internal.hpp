@@ -245,6 +245,30 @@ struct alignas(16) WinRun {
 // array (4 MiB).
 constexpr int ADJ_NOALLOC_COUNTERS = 1 << 20;
 
+// Plane-major rows of at most PLANE_ME entries (copies, zero rows, b rows, the
+// 4-point interpolation rows): one table over all segments.  Within a block
+// the rows go by destination cell, so that the ghosts at the end of one grid
+// line and at the start of the next, which are neighbours in memory, are
+// written together; runs of PLANE_RUN rows go by their position inside their
+// block, so that the runs of different blocks that read and write the same
+// lines follow each other, and are joined to pieces of at most p_rows rows,
+// one workgroup each.  Where rows have several entries, each piece lists its
+// distinct (source cell, rotation) pairs, at most PLANE_UCAP, in cell order.
+// Measured (C384 x 256 FP64, cold): pieces of one block's rows 78.2 us, runs
+// of 64 rows 74.5 (with 8 planes, before non-temporal stores).
+constexpr int PLANE_ME = 4, PLANE_MAXROWS = 256, PLANE_RUN = 64, PLANE_UCAP = 512;
+// planes per workgroup: 4 against 8 64.5 and 65.7 us at C384 x 256 FP64, 5.0
+// and 6.8 us at C203 x 8 (the row records are read twice as often, but twice
+// the workgroups are in flight)
+constexpr int PLANE_PB = 4;
+constexpr int PLANE_ADJ_BLOCK = 256;  // threads of the plane-major adjoint's workgroups
+// meta bits of a row: entries and its b; of a row or source: component rotation code
+constexpr int32_t PM_ROT_SHIFT = 4, PM_HAS_B = 1 << 8, PM_B_INNER = 1 << 9, PM_B_ONLY = 1 << 10;
+struct alignas(16) PlanePiece {
+  int32_t row0, nrows;     // rows of the table
+  int32_t first_u, nu;     // distinct sources (several entries per row)
+};
+
 // Adjoint: one entry per (source cell, ghost row) contribution, sorted by
 // source cell then ghost cell.
 struct CscHost {
@@ -375,6 +399,20 @@ struct HostTables {
   // narrow wide rows (see NarrowTile); seg_narrow marks the segments they take
   std::vector<char> seg_narrow;
   std::vector<NarrowTile> ntiles;
+  // plane-major rows of few entries (see PLANE_ROWS); seg_plane marks the segments they take
+  std::vector<char> seg_plane;
+  int32_t p_me = 1;                // entries per row of the table (1 or PLANE_ME)
+  int32_t p_rows = 64;             // rows per piece at most
+  int32_t p_maxu = 0;              // largest nu over the pieces (LDS sizing)
+  std::vector<PlanePiece> p_pieces;
+  std::vector<int32_t> p_dst;      // destination cell
+  std::vector<int32_t> p_meta;
+  std::vector<int64_t> p_brow;     // offset of the row's first b value (PM_HAS_B)
+  std::vector<int32_t> p_col;      // one entry per row: source cell
+  std::vector<uint16_t> p_slot;    // several: sources of the piece, PLANE_ME per row
+  std::vector<double> p_w;
+  std::vector<int32_t> p_ucell;    // distinct sources of the pieces: cell, rotation code
+  std::vector<int32_t> p_urot;
   // sliding-window rows (see WinRun); seg_win marks the segments they take
   std::vector<char> seg_win;
   std::vector<WinRun> wruns;
@@ -445,6 +483,15 @@ struct Plan {
   const int32_t* d_w_rp = nullptr;
   const void* d_w_ent = nullptr;  // packed {weight, slot * values per slice} per entry
   const NarrowTile* d_ntiles = nullptr;
+  const PlanePiece* d_p_pieces = nullptr;
+  const int32_t* d_p_dst = nullptr;
+  const int32_t* d_p_meta = nullptr;
+  const int64_t* d_p_brow = nullptr;
+  const int32_t* d_p_col = nullptr;
+  const uint16_t* d_p_slot = nullptr;
+  const void* d_p_w = nullptr;
+  const int32_t* d_p_ucell = nullptr;
+  const int32_t* d_p_urot = nullptr;
   const WinRun* d_wruns = nullptr;  // in the tile allocation (depends on the launch shape)
   uint64_t tile_gen = 0;            // bumped whenever the tile tables are rebuilt on the device
   const int32_t* d_dr_cell = nullptr;
@@ -553,6 +600,7 @@ struct ConsumerHost {
 void compile_plan(const Program& prog, const Layout& lay, int dtype, Plan& plan);
 void build_tiles(Plan& plan, const hbc_tune& t);
 hbc_tune default_tune(const Plan& plan);
+int plane_adjoint_lanes(const Plan& plan);
 bool windows_possible(const Plan& plan);
 void build_csc(Plan& plan);
 void compute_stencil_info(Plan& plan);

@@ -172,136 +172,72 @@ __device__ __forceinline__ int64_t rot_slot(const PlanDesc& d, int rot, int64_t 
   return d.vec_lo + p * d.vec_stride + off;
 }
 
-// Plane-major tile: rows [row0, row0 + nrows) of segment s, all inner values.
-// Consecutive threads take consecutive rows (neighbouring ghost cells are
-// neighbours in every plane), the lpr thread sets of a workgroup take planes
-// l = lane, lane + lpr, ...; a thread reads its row's columns and weights
-// once and then works through its planes PB at a time, all loads of the PB
-// planes issued before any arithmetic or store.
+// Plane-major tile of a general ELL/CSR segment s: rows [row0, row0 + nrows),
+// planes [p0, p0 + np), np <= PB.  The lanes take consecutive rows
+// (neighbouring ghost cells are neighbours in every plane); a lane reads each
+// entry once for the PB planes, and issues its loads of all of them before any
+// arithmetic.  The planes are the same for every lane, so their bases and
+// rotations are scalar.
 constexpr int PB = 8;
 
 template <typename T>
-__device__ __forceinline__ void run_tile_pm(const PlanDesc& d, const DevSeg& s, int64_t row0, int nrows,
-                                            bool zero_only, int tid, int nthr) {
-  const int lpr = 1 << d.lpr_shift;
-  const int rp = nthr >> d.lpr_shift;  // rows per pass
-  const int rsub = tid % rp, lane = tid / rp;
-  const int64_t nvec = d.inner;
+__device__ __forceinline__ void run_tile_pm(const PlanDesc& d, const DevSeg& s, int row0, int nrows, int64_t p0,
+                                            int np, bool zero_only, int r0, int rstep) {
   T* __restrict__ f = static_cast<T*>(d.field);
-  const int kind = zero_only ? (int)SEG_ZERO : s.kind;
-  const bool add_b = !zero_only && s.has_b;
-  const bool narrow = kind == SEG_ELL && s.width <= 4;
-  for (int r = rsub; r < nrows; r += rp) {
-    const int64_t row = row0 + r;
-    uint32_t q = (uint32_t)row;
-    int64_t dst = s.dst_base, src = s.src_base;
-    // every SEG_MAXD dimension (unused ones have extent 1 and stride 0), so
-    // that the segment's arrays are read at constant indices, from registers
+  T* out[PB];
+  const T* in[PB];
+  T sign[PB];
 #pragma unroll
-    for (int k = SEG_MAXD - 1; k >= 0; --k) {
-      const uint32_t e = (uint32_t)s.ext[k];
-      const uint32_t c = q % e;
-      q /= e;
-      dst += (int64_t)c * s.dst_stride[k];
-      src += (int64_t)c * s.src_stride[k];
-    }
-    const T* bp = nullptr;
-    if (add_b) bp = static_cast<const T*>(d.bval) + s.brow + row * s.b_inner;
-    int32_t col[4] = {-1, -1, -1, -1};
-    T wt[4] = {T(0), T(0), T(0), T(0)};
-    if (narrow) {
-      const int64_t e0 = s.tab + row * s.width;
+  for (int u = 0; u < PB; ++u) {
+    const int64_t l = p0 + min(u, np - 1);
+    out[u] = f + l * d.ls;
+    in[u] = f + rot_slot<T>(d, s.rot, l, sign[u]) * d.ls;
+  }
+  for (int r = r0; r < nrows; r += rstep) {
+    const int64_t row = (int64_t)row0 + r;
+    const int64_t dst = d.row_dst[s.row_base + row];
+    T y[PB];
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
-        if (m < s.width) {
-          col[m] = d.ell_col[e0 + m];
-          wt[m] = static_cast<const T*>(d.ell_val)[e0 + m];
-        }
-    }
-    for (int64_t v0 = lane; v0 < nvec; v0 += (int64_t)lpr * PB) {
-      int64_t l[PB], sl[PB];
-      T sign[PB];
-      bool ok[PB];
-#pragma unroll
-      for (int u = 0; u < PB; ++u) {
-        const int64_t v = v0 + (int64_t)u * lpr;
-        ok[u] = v < nvec;
-        l[u] = ok[u] ? v : v0;
-        sign[u] = T(1);
-        sl[u] = (kind == SEG_MAP || kind == SEG_ELL || kind == SEG_CSR) ? rot_slot<T>(d, s.rot, l[u], sign[u]) : l[u];
+    for (int u = 0; u < PB; ++u) y[u] = T(0);
+    if (!zero_only) {
+      int64_t e0, e1;
+      const int32_t* cols;
+      const T* vals;
+      if (s.kind == SEG_ELL) {
+        e0 = s.tab + row * s.width;
+        e1 = e0 + s.width;
+        cols = d.ell_col;
+        vals = static_cast<const T*>(d.ell_val);
+      } else {
+        e0 = d.csr_ptr[s.tab + row];
+        e1 = d.csr_ptr[s.tab + row + 1];
+        cols = d.csr_col;
+        vals = static_cast<const T*>(d.csr_val);
       }
-      T y[PB];
-      if (kind == SEG_MAP) {
+      bool first = true;
+      for (int64_t e = e0; e < e1; ++e) {
+        const int32_t c = cols[e];
+        if (c < 0) continue;
+        const T w = vals[e];
         T x[PB];
 #pragma unroll
-        for (int u = 0; u < PB; ++u) x[u] = f[src * d.cs + sl[u] * d.ls];
-#pragma unroll
-        for (int u = 0; u < PB; ++u) y[u] = (T(s.w) * sign[u]) * x[u];
-      } else if (narrow) {
-        T x[PB][4];
+        for (int u = 0; u < PB; ++u)
+          if (u < np) x[u] = in[u][(int64_t)c];
 #pragma unroll
         for (int u = 0; u < PB; ++u)
-#pragma unroll
-          for (int m = 0; m < 4; ++m) x[u][m] = col[m] >= 0 ? f[(int64_t)col[m] * d.cs + sl[u] * d.ls] : T(0);
-#pragma unroll
-        for (int u = 0; u < PB; ++u) {
-          T acc = T(0);
-          bool first = true;
-#pragma unroll
-          for (int m = 0; m < 4; ++m)
-            if (col[m] >= 0) {
-              acc = first ? wt[m] * x[u][m] : fma(wt[m], x[u][m], acc);
-              first = false;
-            }
-          y[u] = sign[u] * acc;
-        }
-      } else if (kind == SEG_ELL || kind == SEG_CSR) {
-        int64_t e0, e1;
-        const int32_t* cols;
-        const T* vals;
-        if (kind == SEG_ELL) {
-          e0 = s.tab + row * s.width;
-          e1 = e0 + s.width;
-          cols = d.ell_col;
-          vals = static_cast<const T*>(d.ell_val);
-        } else {
-          e0 = d.csr_ptr[s.tab + row];
-          e1 = d.csr_ptr[s.tab + row + 1];
-          cols = d.csr_col;
-          vals = static_cast<const T*>(d.csr_val);
-        }
-        T acc[PB];
-#pragma unroll
-        for (int u = 0; u < PB; ++u) acc[u] = T(0);
-        bool first = true;
-        for (int64_t e = e0; e < e1; ++e) {
-          const int32_t c = cols[e];
-          if (c < 0) continue;
-          const T w = vals[e];
-          T x[PB];
-#pragma unroll
-          for (int u = 0; u < PB; ++u) x[u] = f[(int64_t)c * d.cs + sl[u] * d.ls];
-#pragma unroll
-          for (int u = 0; u < PB; ++u) acc[u] = first ? w * x[u] : fma(w, x[u], acc[u]);
-          first = false;
-        }
-#pragma unroll
-        for (int u = 0; u < PB; ++u) y[u] = sign[u] * acc[u];
-      } else {  // zero rows, or b-only rows
-#pragma unroll
-        for (int u = 0; u < PB; ++u) y[u] = T(0);
+          if (u < np) y[u] = first ? w * x[u] : fma(w, x[u], y[u]);
+        first = false;
       }
-      if (add_b) {
+      const T* bp = static_cast<const T*>(d.bval) + s.brow + row * s.b_inner;
 #pragma unroll
-        for (int u = 0; u < PB; ++u) {
-          const T bb = s.b_inner == 1 ? bp[0] : bp[l[u]];
-          y[u] = (kind == SEG_VEC) ? bb : y[u] + bb;
-        }
+      for (int u = 0; u < PB; ++u) {
+        y[u] = sign[u] * y[u];
+        if (s.has_b && u < np) y[u] = y[u] + (s.b_inner == 1 ? bp[0] : bp[p0 + u]);
       }
-#pragma unroll
-      for (int u = 0; u < PB; ++u)
-        if (ok[u]) f[dst * d.cs + l[u] * d.ls] = y[u];
     }
+#pragma unroll
+    for (int u = 0; u < PB; ++u)
+      if (u < np) __builtin_nontemporal_store(y[u], &out[u][dst]);
   }
 }
 
@@ -1214,13 +1150,146 @@ __global__ __launch_bounds__(256) void k_apply_rows(PlanDesc d, const RowTile* _
   }
 }
 
+// Plane-major applies: one workgroup per (group of planes, piece of rows).
+// Items are ordered by plane group first and dealt to the XCDs in contiguous
+// ranges, so that an XCD works through a few planes at a time with every strip
+// of every block, and the lines that strips share (a line of a face's slow
+// index holds the ghosts and sources of both its ends) meet in one L2.
+__device__ __forceinline__ int plane_item(int it, int items) {
+  const int q = items >> 3, rem = items & 7, x = it & 7;
+  return x * q + min(x, rem) + (it >> 3);
+}
+
+// Rows of general width, by segment tiles.
 template <typename T>
 __global__ __launch_bounds__(256) void k_apply_pm(PlanDesc d, const DevTile* __restrict__ tiles, int ntiles,
-                                                   int zero_only) {
-  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+                                                  int items, int zero_only) {
+  for (int it = blockIdx.x; it < items; it += gridDim.x) {
+    const int item = plane_item(it, items), pg = item / ntiles, t = item - pg * ntiles;
+    const int64_t p0 = (int64_t)pg * PB;
     const DevTile tl = tiles[t];
     const DevSeg s = d.segs[tl.seg];
-    run_tile_pm<T>(d, s, tl.row0, tl.nrows, zero_only != 0, threadIdx.x, blockDim.x);
+    run_tile_pm<T>(d, s, (int)tl.row0, tl.nrows, p0, (int)min<int64_t>(PB, d.inner - p0), zero_only != 0,
+                   (int)threadIdx.x, (int)blockDim.x);
+  }
+}
+
+// Rows of few entries (see PlanePiece).  The planes are uniform, the rotation
+// is the lane's: it picks the source plane of a vector component and its sign.
+// ME > 1: the piece's distinct sources are staged in LDS, each loaded once per
+// plane, and the rows sum from LDS.  Neighbouring rows of a 4-point strip share
+// three of their four sources; read directly, the later loads hit lines that
+// are still on their way to the L1, which stalls it (TCP_PENDING_STALL: 70 %
+// of the cycles; 99 us at C384 x 256 FP64).
+// C384 x 256 FP64: 142 us with one workgroup per segment tile over all planes
+// -> 96 us with planes dealt to the XCDs -> 74 us staged -> 68.7 us with
+// non-temporal stores -> 64.5 us with 4 planes.  Bound by the lines touched:
+// the strips of a slow index write 48-byte pieces and read 24-byte ones, each
+// in a line of its own in every plane (stores alone 58 us, 1.5 M requests).
+struct PlaneRows {
+  const PlanePiece* pieces;
+  const int32_t* dst;
+  const int32_t* meta;
+  const int64_t* brow;
+  const int32_t* col;
+  const uint16_t* slot;
+  const void* w;
+  const int32_t* ucell;
+  const int32_t* urot;
+  int32_t npieces, ustride;  // ustride: LDS values per plane
+  int32_t vec_g0, vec_ng;    // plane groups of the vector's components (vec_ng each, 0: not whole groups)
+};
+
+template <typename T, int ME, bool ROT>
+__global__ __launch_bounds__(256) void k_apply_planes(PlanDesc d, PlaneRows t, int items, int zero_only) {
+  constexpr int PB = PLANE_PB;
+  extern __shared__ __align__(16) unsigned char pl_smem[];
+  T* lds = reinterpret_cast<T*>(pl_smem);
+  const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
+  T* __restrict__ f = static_cast<T*>(d.field);
+  for (int it = blockIdx.x; it < items; it += gridDim.x) {
+    const int item = plane_item(it, items);
+    int pg = item / t.npieces;
+    const PlanePiece pc = t.pieces[item - pg * t.npieces];
+    // the groups of the two vector components in turn: rotated rows of one read the planes of the other
+    const int k = pg - t.vec_g0;
+    if (ROT && k >= 0 && k < 2 * t.vec_ng) pg = t.vec_g0 + (k >> 1) + (k & 1) * t.vec_ng;
+    const int64_t p0 = (int64_t)pg * PB;
+    const int np = (int)min<int64_t>(PB, d.inner - p0);
+    // source plane of plane l under a lane's rotation, and the sign
+    auto source = [&](int64_t l, int rot, T& sign) -> const T* {
+      sign = T(1);
+      if constexpr (ROT) {
+        const int64_t off = l - d.vec_lo;
+        const int a = off >= 0 && off < d.vec_len ? 0 : off >= d.vec_stride && off < d.vec_stride + d.vec_len ? 1 : -1;
+        if (a >= 0) {  // uniform
+          if (rot & (2 << a)) sign = T(-1);
+          if (rot & 1) return f + (a == 0 ? l + d.vec_stride : l - d.vec_stride) * d.ls;
+        }
+      }
+      return f + l * d.ls;
+    };
+    if constexpr (ME > 1) {
+      if (it != (int)blockIdx.x) __syncthreads();  // the last item's rows are summed
+      if (!zero_only)
+        for (int i = tid; i < pc.nu; i += nthr) {
+          const int64_t cell = t.ucell[pc.first_u + i];
+          const int rot = ROT ? t.urot[pc.first_u + i] : 0;
+          T x[PB], sign[PB];
+#pragma unroll
+          for (int u = 0; u < PB; ++u)
+            if (u < np) x[u] = source(p0 + u, rot, sign[u])[cell];
+#pragma unroll
+          for (int u = 0; u < PB; ++u)
+            if (u < np) lds[u * t.ustride + i] = sign[u] * x[u];
+        }
+    }
+    for (int r = tid; r - tid < pc.nrows; r += nthr) {
+      const bool live = r < pc.nrows;
+      const int64_t row = pc.row0 + (live ? r : 0);
+      const int64_t dst = t.dst[row];
+      const int meta = t.meta[row];
+      const int ne = zero_only ? 0 : meta & 15;
+      const Pack<T, ME> w = ldv<T, ME>(static_cast<const T*>(t.w) + row * ME);
+      T y[PB];
+      if constexpr (ME > 1) {
+        const Pack<uint16_t, ME> c = ldv<uint16_t, ME>(t.slot + row * ME);
+        if (r == tid) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+          y[u] = T(0);
+          if (u < np) {
+            const T* xl = lds + u * t.ustride;
+#pragma unroll
+            for (int m = 0; m < ME; ++m)
+              if (m < ne) y[u] = m == 0 ? w.v[0] * xl[c.v[0]] : fma(w.v[m], xl[c.v[m]], y[u]);
+          }
+        }
+      } else {
+        const int64_t col = t.col[row];
+        const int rot = meta >> PM_ROT_SHIFT;
+        T x[PB], sign[PB];
+        if (ne > 0) {
+#pragma unroll
+          for (int u = 0; u < PB; ++u)
+            if (u < np) x[u] = source(p0 + u, rot, sign[u])[col];
+        }
+#pragma unroll
+        for (int u = 0; u < PB; ++u) y[u] = ne > 0 && u < np ? sign[u] * (w.v[0] * x[u]) : T(0);
+      }
+      if (!zero_only && (meta & PM_HAS_B)) {
+        const T* bp = static_cast<const T*>(d.bval) + t.brow[row];
+#pragma unroll
+        for (int u = 0; u < PB; ++u)
+          if (u < np) {
+            const T bb = (meta & PM_B_INNER) ? bp[p0 + u] : bp[0];
+            y[u] = (meta & PM_B_ONLY) ? bb : y[u] + bb;
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < PB; ++u)
+        if (u < np && live) __builtin_nontemporal_store(y[u], &f[(p0 + u) * d.ls + dst]);
+    }
   }
 }
 
@@ -2421,21 +2490,29 @@ void device_free_plan(Plan& p) {
 void device_upload_plan(Plan& p) {
   Packer pk;
   const HostTables& T = p.host;
+  // a plane-major plan whose rows are all in the pieces' table reads no segment tables
+  const bool tabs = p.layout.order == HBC_POINT_MAJOR || !T.tiles.empty();
+  const std::vector<int32_t> none32;
+  const std::vector<int64_t> none64;
+  const std::vector<double> none;
   size_t o_segs = pk.vec(T.segs);
-  size_t o_ellc = pk.vec(T.ell_col);
-  size_t o_ellv = pk.reals(T.ell_val, p.dtype);
-  size_t o_csrp = pk.vec(T.csr_ptr);
-  size_t o_csrc = pk.vec(T.csr_col);
-  size_t o_csrv = pk.reals(T.csr_val, p.dtype);
+  size_t o_ellc = pk.vec(tabs ? T.ell_col : none32);
+  size_t o_ellv = pk.reals(tabs ? T.ell_val : none, p.dtype);
+  size_t o_csrp = pk.vec(tabs ? T.csr_ptr : none64);
+  size_t o_csrc = pk.vec(tabs ? T.csr_col : none32);
+  size_t o_csrv = pk.reals(tabs ? T.csr_val : none, p.dtype);
   size_t o_b = pk.reals(T.bval, p.dtype);
-  size_t o_rd = pk.vec(T.row_dst);
-  size_t o_rs = pk.vec(T.row_src);
+  size_t o_rd = pk.vec(tabs ? T.row_dst : none32);
+  size_t o_rs = pk.vec(tabs ? T.row_src : none32);
   size_t o_wt = pk.vec(T.wtiles);
   size_t o_wu = pk.vec(T.w_ucell);
   size_t o_wr = pk.vec(T.w_row);
   size_t o_wp = pk.vec(T.w_rp);
   size_t o_we = pk.wide_entries(T.w_entw, T.w_ents, p.dtype, wide_slice_bytes(p) / (p.dtype == HBC_F64 ? 8 : 4));
   size_t o_nt = pk.vec(T.ntiles);
+  size_t o_pp = pk.vec(T.p_pieces), o_pd = pk.vec(T.p_dst), o_pm = pk.vec(T.p_meta), o_pb = pk.vec(T.p_brow),
+         o_pc = pk.vec(T.p_col), o_ps = pk.vec(T.p_slot), o_pw = pk.reals(T.p_w, p.dtype), o_pu = pk.vec(T.p_ucell),
+         o_pr = pk.vec(T.p_urot);
   size_t o_drc = pk.vec(T.dr_cell);
   size_t o_drp = pk.vec(T.dr_ptr);
   size_t o_drk = pk.vec(T.dr_col);
@@ -2468,6 +2545,15 @@ void device_upload_plan(Plan& p) {
   p.d_w_rp = reinterpret_cast<const int32_t*>(b + o_wp);
   p.d_w_ent = b + o_we;
   p.d_ntiles = reinterpret_cast<const NarrowTile*>(b + o_nt);
+  p.d_p_dst = reinterpret_cast<const int32_t*>(b + o_pd);
+  p.d_p_meta = reinterpret_cast<const int32_t*>(b + o_pm);
+  p.d_p_brow = reinterpret_cast<const int64_t*>(b + o_pb);
+  p.d_p_col = reinterpret_cast<const int32_t*>(b + o_pc);
+  p.d_p_w = b + o_pw;
+  p.d_p_pieces = reinterpret_cast<const PlanePiece*>(b + o_pp);
+  p.d_p_slot = reinterpret_cast<const uint16_t*>(b + o_ps);
+  p.d_p_ucell = reinterpret_cast<const int32_t*>(b + o_pu);
+  p.d_p_urot = reinterpret_cast<const int32_t*>(b + o_pr);
   p.d_dr_cell = reinterpret_cast<const int32_t*>(b + o_drc);
   p.d_dr_ptr = reinterpret_cast<const int64_t*>(b + o_drp);
   p.d_dr_col = reinterpret_cast<const int32_t*>(b + o_drk);
@@ -2758,6 +2844,38 @@ static void launch_win(const Plan& p, const PlanDesc& d, hipStream_t st, bool ze
   HIP_CHECK(hipGetLastError());
 }
 
+// Plane-major plans: the rows of few entries, then the tiles of the others.
+template <typename T>
+static void launch_planes(const Plan& p, const PlanDesc& d, hipStream_t st, int z) {
+  const int64_t rows = (p.layout.inner + PLANE_PB - 1) / PLANE_PB * (int64_t)p.host.p_pieces.size();
+  const int64_t tiles = (p.layout.inner + PB - 1) / PB * (int64_t)p.host.tiles.size();
+  if (std::max(rows, tiles) >= (int64_t(1) << 31)) fail(HBC_EUNSUPPORTED, "plane-major apply too large for one launch");
+  auto grid = [&](int64_t n) { return dim3((unsigned)(p.tune.persistent > 0 ? std::min<int64_t>(p.tune.persistent, n) : n)); };
+  const dim3 blk(p.tune.block);
+  if (rows > 0) {
+    const int ustride = p.host.p_maxu | 1;
+    const bool whole = d.vec_stride == d.vec_len && d.vec_lo % PLANE_PB == 0 && d.vec_len % PLANE_PB == 0;
+    const PlaneRows t{p.d_p_pieces, p.d_p_dst, p.d_p_meta, p.d_p_brow, p.d_p_col, p.d_p_slot, p.d_p_w, p.d_p_ucell,
+                      p.d_p_urot, (int32_t)p.host.p_pieces.size(), ustride, (int32_t)(d.vec_lo / PLANE_PB),
+                      whole ? (int32_t)(d.vec_len / PLANE_PB) : 0};
+    const size_t lds = p.host.p_me > 1 && !z ? (size_t)ustride * PLANE_PB * sizeof(T) : 0;
+    const bool rot = d.vec_len > 0;
+    if (p.host.p_me == 1 && rot)
+      HBC_LAUNCH((k_apply_planes<T, 1, true>), grid(rows), blk, lds, st, d, t, (int)rows, z);
+    else if (p.host.p_me == 1)
+      HBC_LAUNCH((k_apply_planes<T, 1, false>), grid(rows), blk, lds, st, d, t, (int)rows, z);
+    else if (rot)
+      HBC_LAUNCH((k_apply_planes<T, PLANE_ME, true>), grid(rows), blk, lds, st, d, t, (int)rows, z);
+    else
+      HBC_LAUNCH((k_apply_planes<T, PLANE_ME, false>), grid(rows), blk, lds, st, d, t, (int)rows, z);
+    HIP_CHECK(hipGetLastError());
+  }
+  if (tiles > 0) {
+    HBC_LAUNCH((k_apply_pm<T>), grid(tiles), blk, 0, st, d, p.d_tiles, (int)p.host.tiles.size(), (int)tiles, z);
+    HIP_CHECK(hipGetLastError());
+  }
+}
+
 template <typename T>
 static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only) {
   const bool pm = p.layout.order == HBC_POINT_MAJOR;
@@ -2804,12 +2922,12 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
     }
   }
   if (has_win) launch_win<T>(p, d, st, zero_only, fold && !has_narrow && !has_wide ? nt : 0);
-  if (fold || grid + dd.grid == 0) return;
   if (!pm) {
-    if (grid > 0) HBC_LAUNCH((k_apply_pm<T>), dim3(grid), dim3(blk), 0, st, d, p.d_tiles, nt, z);
-  } else {
-    launch_rows<T>(d, st, grid, blk, p.d_rtiles, nt, z, dd);
+    launch_planes<T>(p, d, st, z);
+    return;
   }
+  if (fold || grid + dd.grid == 0) return;
+  launch_rows<T>(d, st, grid, blk, p.d_rtiles, nt, z, dd);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -2980,8 +3098,11 @@ static void launch_adjoint_t(const Plan& p, const PlanDesc& d, hipStream_t st, i
   const int nt = (int)p.host.adj_tiles.size();
   if (nt > 0) {
     const int blk = p.tune.block;
-    if (p.layout.order == HBC_PLANE_MAJOR)
-      HBC_LAUNCH((k_adjoint<T, 1, true, false>), dim3(nt), dim3(blk), 0, st, d, a, p.d_adj_tiles, nt);
+    if (p.layout.order == HBC_PLANE_MAJOR) {
+      PlanDesc dp = d;
+      dp.lpr_shift = ilog2(plane_adjoint_lanes(p));
+      HBC_LAUNCH((k_adjoint<T, 1, true, false>), dim3(nt), dim3(PLANE_ADJ_BLOCK), 0, st, dp, a, p.d_adj_tiles, nt);
+    }
     else if (p.vec == 4 && d.nt)
       HBC_LAUNCH((k_adjoint<T, 4, false, true>), dim3(nt), dim3(blk), 0, st, d, a, p.d_adj_tiles, nt);
     else if (p.vec == 4)
@@ -3578,8 +3699,8 @@ void device_batch_stats(const Batch* b, hbc_stats* out) { *out = b->stats; }
 // Generation of the kernels' performance, part of every autotune cache key:
 // a choice stored by a build whose kernels time differently is not reused
 // (bumped with such changes; 2: window loads at raised priority, where runs
-// of 4 turned from the fastest to among the slowest).
-constexpr int TUNE_CACHE_GEN = 2;
+// of 4 turned from the fastest to among the slowest; 3: plane-major pieces).
+constexpr int TUNE_CACHE_GEN = 3;
 
 static std::string batch_key(const Batch* b) {
   int dev = 0;

@@ -75,6 +75,20 @@ int64_t Grid::cell(int b, const int64_t* c) const {
 
 bool Grid::unlinear(int64_t lin, int64_t* c) const {
   if (lin < 0) return false;
+  if (lin <= UINT32_MAX) {  // 32-bit divisions take a third of the time
+    uint32_t k = (uint32_t)lin;
+    for (int d = nd - 1; d >= 0; --d) {
+      if (hi[d] - lo[d] > UINT32_MAX) {
+        c[d] = lo[d] + k;
+        k = 0;
+        continue;
+      }
+      const uint32_t e = (uint32_t)(hi[d] - lo[d]);
+      c[d] = lo[d] + k % e;
+      k /= e;
+    }
+    return k == 0;
+  }
   for (int d = nd - 1; d >= 0; --d) {
     int64_t e = hi[d] - lo[d];
     c[d] = lo[d] + lin % e;
@@ -163,10 +177,13 @@ void for_box_order(const Box& b, const std::vector<int>& order, F&& f) {
 }
 
 // Data cell of a global linear index; HBC_ERANGE if it is not a data cell.
-int64_t data_cell_of_linear(const Grid& g, int64_t lin) {
+// hint: a block tried first, and the one found (neighbouring entries read one
+// block).
+int64_t data_cell_of_linear(const Grid& g, int64_t lin, int& hint) {
   int64_t c[HBC_MAX_DIM];
   if (!g.unlinear(lin, c)) fail(HBC_ERANGE, "column index " + std::to_string(lin) + " is outside the global box");
-  int b = g.owner(c);
+  if (hint >= 0 && g.blocks[hint].data.contains(c)) return g.cell(hint, c);
+  const int b = hint = g.owner(c);
   if (b < 0 || !g.blocks[b].data.contains(c))
     fail(HBC_ERANGE, "column index " + std::to_string(lin) + " is not a data cell");
   return g.cell(b, c);
@@ -445,6 +462,7 @@ void compile_plan(const Program& prog, const Layout& lay, int dtype, Plan& plan)
   hbc_stats& st = plan.stats;
   std::memset(&st, 0, sizeof(st));
   std::vector<int64_t> sources;
+  int hint = -1;  // block of the last column
   const int nd = g.nd;
   int64_t row_base = 0;
 
@@ -536,7 +554,7 @@ void compile_plan(const Program& prog, const Layout& lay, int dtype, Plan& plan)
             seg.flags |= SEGF_ELL_PADDED;
             continue;
           }
-          int64_t cell = data_cell_of_linear(g, lin);
+          int64_t cell = data_cell_of_linear(g, lin, hint);
           T.ell_col.push_back((int32_t)cell);
           T.ell_val.push_back(v);
           sources.push_back(cell);
@@ -562,11 +580,11 @@ void compile_plan(const Program& prog, const Layout& lay, int dtype, Plan& plan)
             int64_t k = box_linear(s.rows, r);
             for (int q = 0; q < s.width; ++q)
               if (s.cols[k * s.width + q] >= 0)
-                ents.emplace_back(data_cell_of_linear(g, s.cols[k * s.width + q]), s.vals[k * s.width + q]);
+                ents.emplace_back(data_cell_of_linear(g, s.cols[k * s.width + q], hint), s.vals[k * s.width + q]);
           } else if (s.kind == SUB_CSR) {
             int64_t k = box_linear(s.rows, r);
             for (int64_t q = s.ptr[k]; q < s.ptr[k + 1]; ++q)
-              ents.emplace_back(data_cell_of_linear(g, s.cols[q]), s.vals[q]);
+              ents.emplace_back(data_cell_of_linear(g, s.cols[q], hint), s.vals[q]);
           }
         }
         if (mats.size() > 1) {  // sum duplicate columns
@@ -684,7 +702,7 @@ void compile_plan(const Program& prog, const Layout& lay, int dtype, Plan& plan)
       T.dr_cell.push_back((int32_t)g.cell(b, r));
       T.dr_ptr.push_back((int64_t)T.dr_col.size());
       for (int64_t e = ds.ptr[k]; e < ds.ptr[k + 1]; ++e) {
-        const int64_t cell = data_cell_of_linear(g, ds.cols[e]);
+        const int64_t cell = data_cell_of_linear(g, ds.cols[e], hint);
         T.dr_col.push_back((int32_t)cell);
         T.dr_val.push_back(ds.vals[e]);
         sources.push_back(cell);
@@ -706,8 +724,13 @@ void compile_plan(const Program& prog, const Layout& lay, int dtype, Plan& plan)
   st.ghost_cells_live = live_ghosts;
   if ((prog.flags & HBC_STRICT_COVER) && live_ghosts - st.rows_covered > 0)
     fail(HBC_EUNCOVERED, std::to_string(live_ghosts - st.rows_covered) + " ghost cells are covered by no sub-matrix");
-  std::sort(sources.begin(), sources.end());
-  st.unique_sources = (int64_t)(std::unique(sources.begin(), sources.end()) - sources.begin());
+  std::vector<bool> seen((size_t)g.ncells, false);
+  st.unique_sources = 0;
+  for (int64_t c : sources)
+    if (!seen[(size_t)c]) {
+      seen[(size_t)c] = true;
+      ++st.unique_sources;
+    }
   st.segments = (int64_t)T.segs.size();
   st.ghost_values = st.rows_covered * lay.inner;
   const double es = dtype == HBC_F64 ? 8.0 : 4.0;
@@ -772,6 +795,15 @@ bool windows_possible(const Plan& plan) {
   return false;
 }
 
+// Rows per piece of the plane-major kernel: 256 (rows of one piece share
+// sources), fewer while that leaves less than 4 workgroups per CU.
+static int32_t plane_rows(const Plan& plan) {
+  const int64_t groups = (plan.layout.inner + PLANE_PB - 1) / PLANE_PB;
+  int32_t n = PLANE_MAXROWS;
+  while (n > 64 && plan.stats.rows_covered / n * groups < 256 * 4) n /= 2;
+  return n;
+}
+
 hbc_tune default_tune(const Plan& plan) {
   hbc_tune t{};
   t.block = 256;
@@ -784,10 +816,9 @@ hbc_tune default_tune(const Plan& plan) {
     int64_t nacc = (nvec + plan.unroll - 1) / plan.unroll;
     t.lanes_per_row = (int32_t)std::min<int64_t>(t.block, pow2_ceil(nacc));
   } else {
-    // plane-major: 8 planes per thread and batch, up to 16 thread sets over
-    // the planes (16 consecutive rows per wavefront and plane)
-    const int64_t sets = (plan.layout.inner + 7) / 8;
-    t.lanes_per_row = (int32_t)std::min<int64_t>(16, pow2_ceil(sets));
+    // plane-major: one row per lane; at least two wavefronts to stage a piece
+    t.lanes_per_row = 1;
+    t.block = std::max(128, plane_rows(plan));
   }
   const int64_t rows_per_pass = t.block / t.lanes_per_row;
   // Short tiles keep many workgroups in flight (the apply is latency bound per
@@ -795,8 +826,8 @@ hbc_tune default_tune(const Plan& plan) {
   // row group when groups take contiguous runs of rows, else about 4096 tiles
   // in all.
   int64_t rpt;
-  if (plan.layout.order != HBC_POINT_MAJOR && t.lanes_per_row > 1) {
-    rpt = rows_per_pass;  // one pass of rows over all planes per tile
+  if (plan.layout.order != HBC_POINT_MAJOR) {
+    rpt = rows_per_pass;  // one row per lane
   } else if (t.lanes_per_row >= CHUNK_LPR) {
     rpt = rows_per_pass * rows_per_batch(t.lanes_per_row);
   } else {
@@ -807,6 +838,11 @@ hbc_tune default_tune(const Plan& plan) {
   if (windows_possible(plan)) rpt = WIN_DEFAULT_ROWS;  // rows per sliding-window run
   t.rows_per_tile = (int32_t)rpt;
   return t;
+}
+
+// Lanes per source of the plane-major adjoint (8 planes per lane, at most 16 lanes).
+int plane_adjoint_lanes(const Plan& plan) {
+  return (int)std::min<int64_t>(16, pow2_ceil((plan.layout.inner + 7) / 8));
 }
 
 // Segment rows in wide-tile order: the thinnest box dimension innermost, the
@@ -948,6 +984,135 @@ static void build_narrow(Plan& plan) {
   }
 }
 
+// Plane-major rows of few entries (see PlanePiece).
+static void build_planes(Plan& plan) {
+  HostTables& T = plan.host;
+  T.seg_plane.assign(T.segs.size(), 0);
+  if (plan.layout.order != HBC_PLANE_MAJOR) return;
+  std::vector<uint64_t> rows;  // destination cell << 32 | row
+  std::vector<int32_t> seg_of(T.row_dst.size(), -1);
+  auto dst_of = [](uint64_t k) { return (int64_t)(k >> 32); };
+  T.p_me = 1;
+  for (size_t si = 0; si < T.segs.size(); ++si) {
+    const DevSeg& sg = T.segs[si];
+    int64_t most = sg.kind == SEG_MAP ? 1 : 0;
+    if (sg.kind == SEG_ELL) most = sg.width;
+    if (sg.kind == SEG_CSR)
+      for (int64_t r = 0; r < sg.nrows; ++r)
+        most = std::max(most, T.csr_ptr[sg.tab + r + 1] - T.csr_ptr[sg.tab + r]);
+    if (most > PLANE_ME) continue;
+    T.seg_plane[si] = 1;
+    if (most > 1) T.p_me = PLANE_ME;
+    for (int64_t r = 0; r < sg.nrows; ++r) {
+      seg_of[(size_t)(sg.row_base + r)] = (int32_t)si;
+      rows.push_back((uint64_t)T.row_dst[(size_t)(sg.row_base + r)] << 32 | (uint64_t)(sg.row_base + r));
+    }
+  }
+  std::sort(rows.begin(), rows.end());
+  T.p_rows = plane_rows(plan);
+  struct Run {
+    int64_t at;  // cell inside the block
+    size_t first, n;
+  };
+  std::vector<Run> runs;
+  size_t n = 0;
+  for (const Block& b : plan.grid.blocks)
+    while (n < rows.size() && dst_of(rows[n]) < b.first_cell + b.cells) {
+      const size_t first = n;
+      while (n < rows.size() && n - first < (size_t)PLANE_RUN && dst_of(rows[n]) < b.first_cell + b.cells) ++n;
+      runs.push_back(Run{dst_of(rows[first]) - b.first_cell, first, n - first});
+    }
+  std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.at < b.at; });
+  T.p_dst.reserve(rows.size());
+  T.p_meta.reserve(rows.size());
+  T.p_brow.reserve(rows.size());
+  const size_t total = rows.size() * (size_t)T.p_me;
+  T.p_w.assign(total, 0.0);
+  if (T.p_me == 1)
+    T.p_col.assign(total, 0);
+  else
+    T.p_slot.assign(total, 0);
+  // sources of the open piece: (cell << 3 | rotation), and where each is found
+  // (open addressing, at most an eighth full)
+  constexpr uint32_t BUCKETS = 8 * PLANE_UCAP;
+  std::vector<int32_t> bucket(BUCKETS, -1);
+  std::vector<uint64_t> source, by_cell;
+  std::vector<uint16_t> moved;
+  auto find = [&](uint64_t key) {
+    uint32_t at = (uint32_t)(key * 0x9E3779B97F4A7C15ull >> 40) % BUCKETS;
+    while (bucket[at] >= 0 && source[(size_t)bucket[at]] != key) at = (at + 1) % BUCKETS;
+    return at;
+  };
+  PlanePiece pc{0, 0, 0, 0};
+  auto close = [&] {
+    pc.nu = (int32_t)source.size();
+    if (pc.nrows > 0) T.p_pieces.push_back(pc);
+    if (pc.nu > 0) {  // stage in cell order: neighbouring lanes then read neighbouring cells
+      by_cell = source;
+      std::sort(by_cell.begin(), by_cell.end());
+      moved.resize(source.size());
+      for (size_t u = 0; u < by_cell.size(); ++u) {
+        moved[(size_t)bucket[find(by_cell[u])]] = (uint16_t)u;
+        T.p_ucell.push_back((int32_t)(by_cell[u] >> 3));
+        T.p_urot.push_back((int32_t)(by_cell[u] & 7));
+      }
+      for (size_t k = (size_t)pc.row0 * (size_t)T.p_me; k < T.p_dst.size() * (size_t)T.p_me; ++k)
+        T.p_slot[k] = moved[T.p_slot[k]];
+      std::fill(bucket.begin(), bucket.end(), -1);
+      source.clear();
+    }
+    T.p_maxu = std::max(T.p_maxu, pc.nu);
+    pc = PlanePiece{(int32_t)T.p_dst.size(), 0, (int32_t)T.p_ucell.size(), 0};
+  };
+  for (const Run& run : runs) {
+    if (pc.nrows + run.n > (size_t)T.p_rows) close();
+    for (size_t k = run.first; k < run.first + run.n; ++k) {
+      const size_t row = (size_t)(uint32_t)rows[k];
+      const DevSeg& sg = T.segs[(size_t)seg_of[row]];
+      const int64_t r = (int64_t)row - sg.row_base;
+      int32_t ne = 0, cols[PLANE_ME] = {0};
+      double w[PLANE_ME] = {0.0};
+      auto entry = [&](int32_t col, double v) {
+        if (col < 0) return;  // padding
+        cols[ne] = col;
+        w[ne++] = v;
+      };
+      if (sg.kind == SEG_MAP) {
+        entry(T.row_src[row], sg.w);
+      } else if (sg.kind == SEG_ELL) {
+        for (int m = 0; m < sg.width; ++m) entry(T.ell_col[sg.tab + r * sg.width + m], T.ell_val[sg.tab + r * sg.width + m]);
+      } else if (sg.kind == SEG_CSR) {
+        for (int64_t e = T.csr_ptr[sg.tab + r]; e < T.csr_ptr[sg.tab + r + 1]; ++e) entry(T.csr_col[e], T.csr_val[e]);
+      }
+      if ((int64_t)source.size() + ne > PLANE_UCAP) close();
+      const size_t at = T.p_dst.size() * (size_t)T.p_me;
+      for (int32_t m = 0; m < ne; ++m) {
+        T.p_w[at + m] = w[m];
+        if (T.p_me == 1) {
+          T.p_col[at] = cols[m];
+          continue;
+        }
+        const uint64_t key = (uint64_t)cols[m] << 3 | (uint64_t)sg.rot;
+        const uint32_t f = find(key);
+        if (bucket[f] < 0) {
+          bucket[f] = (int32_t)source.size();
+          source.push_back(key);
+        }
+        T.p_slot[at + m] = (uint16_t)bucket[f];
+      }
+      T.p_dst.push_back(T.row_dst[row]);
+      T.p_meta.push_back(ne | (ne > 0 ? sg.rot << PM_ROT_SHIFT : 0));
+      T.p_brow.push_back(0);
+      if (sg.has_b) {
+        T.p_meta.back() |= PM_HAS_B | (sg.b_inner > 1 ? PM_B_INNER : 0) | (sg.kind == SEG_VEC ? PM_B_ONLY : 0);
+        T.p_brow.back() = sg.brow + r * sg.b_inner;
+      }
+      ++pc.nrows;
+    }
+  }
+  close();
+}
+
 // Sliding-window runs (see WinRun).  A segment qualifies when every row is a
 // window (four cells c, c + dl, c + 2 dl, c + 3 dl, dl != 0).  Its rows are
 // cut, in device order, into runs of at most rmax rows in which each row's
@@ -1015,9 +1180,11 @@ void build_tiles(Plan& plan, const hbc_tune& t) {
   if (t.rows_per_tile < 1) fail(HBC_EINVAL, "rows_per_tile must be >= 1");
   if (t.persistent < 0) fail(HBC_EINVAL, "persistent must be >= 0");
   if (t.window_order != 0 && t.window_order != 1) fail(HBC_EINVAL, "window_order must be 0 or 1");
+  if (plan.host.seg_plane.size() != plan.host.segs.size()) build_planes(plan);
   std::vector<DevTile> tiles;
   for (size_t s = 0; s < plan.host.segs.size(); ++s) {
     const DevSeg& sg = plan.host.segs[s];
+    if (plan.host.seg_plane[s]) continue;  // served by the plane-row kernel
     for (int64_t r0 = 0; r0 < sg.nrows; r0 += t.rows_per_tile) {
       DevTile tl;
       tl.seg = (int32_t)s;
@@ -1043,7 +1210,7 @@ void build_tiles(Plan& plan, const hbc_tune& t) {
     out = tiles;
   }
   plan.host.tiles.swap(out);
-  plan.stats.tiles = (int64_t)plan.host.tiles.size();
+  plan.stats.tiles = (int64_t)plan.host.tiles.size() + (int64_t)plan.host.p_pieces.size();
   plan.tune = t;
   // the same cut as point-major row tiles (same XCD-aware order)
   plan.host.rtiles.clear();
@@ -1341,7 +1508,9 @@ void build_csc(Plan& plan) {
   // adjoint tiles: sources grouped so that a tile holds about as many inner
   // values as a forward tile
   const int64_t ns = (int64_t)C.src_cell.size();
-  int64_t per = std::max<int64_t>(plan.tune.block / plan.tune.lanes_per_row, ns / 2048);
+  const int lanes = plan.layout.order == HBC_PLANE_MAJOR ? plane_adjoint_lanes(plan) : plan.tune.lanes_per_row;
+  const int threads = plan.layout.order == HBC_PLANE_MAJOR ? PLANE_ADJ_BLOCK : plan.tune.block;
+  int64_t per = std::max<int64_t>(threads / lanes, ns / 2048);
   per = std::min<int64_t>(per, 16384);
   for (int64_t s = 0; s < ns; s += per)
     plan.host.adj_tiles.push_back(AdjTile{(int32_t)s, (int32_t)std::min<int64_t>(per, ns - s)});
