@@ -138,7 +138,9 @@ typedef struct {
   int64_t rows_window;      /* 4-entry rows on four consecutive points of a grid line, each row's window at
                                the previous row's or one point further (Sec. III-B interpolation rows of a
                                face-edge strip), served by the window kernel: point-major, rows of >= 256
-                               bytes in whole 16-byte vectors; each wavefront loads a run's cells once */
+                               bytes in whole 16-byte vectors; each wavefront loads a run's cells once.
+                               Such rows of other lengths (from 128 bytes) or, with b, below 512 bytes go
+                               through the same kernel in runs of a fixed length and are not counted */
   int64_t window_runs;      /* runs of those rows (at most rows_per_tile rows each) */
 } hbc_stats;
 

@@ -233,6 +233,14 @@ constexpr int WIN_MAXR = 16, WIN_MIN_BYTES = 256, WIN_DEFAULT_ROWS = 8;
 // segments with b: from 512 bytes (C768 x 32 FP64 with b on every strip row:
 // 12.4 us windowed at 256 bytes against 10.7 us with the row kernel)
 constexpr int WIN_MIN_BYTES_B = 512;
+// The other window-shaped rows (shorter, with b, or of a length that vectors do
+// not divide) go in runs of a fixed length, whatever the tune: 6 rows where a
+// run is one slice, else 8.  Measured against the row kernel (C384, cold): FP64
+// x 20 5.3 against 7.6 us, x 137 15.5 against 21.8, FP32 x 33 5.2 against 6.4,
+// x 137 with b 9.4 against 11.8; C768 x 32 FP64 with b 5.4 against 7.3, FP32
+// (128-byte rows) 3.9 against 5.4; at 80 bytes they lose (FP32 x 20 4.4 against
+// 4.2, with b 5.3 against 4.6).
+constexpr int WIN_FIXED_BYTES = 128, WIN_FIXED_ROWS = 6, WIN_FIXED_LONG_ROWS = 8;
 struct alignas(16) WinRun {
   int32_t src0, dl, nrows, nsrc;
   int64_t row_begin;  // first row in the per-row tables (row_dst)
@@ -416,7 +424,9 @@ struct HostTables {
   // sliding-window rows (see WinRun); seg_win marks the segments they take
   std::vector<char> seg_win;
   std::vector<WinRun> wruns;
-  int32_t win_maxr = 0;  // longest run
+  std::vector<WinRun> fruns;  // runs of a fixed length (see WIN_FIXED_BYTES)
+  bool fix_has_b = false;
+  int32_t win_maxr = 0;  // longest run of wruns
   bool win_has_b = false;  // a run with b values (the window launch picks its instance by it)
   // data rows: destination cells, CSR over data cells (absolute pointers)
   std::vector<int32_t> dr_cell;
@@ -493,6 +503,7 @@ struct Plan {
   const int32_t* d_p_ucell = nullptr;
   const int32_t* d_p_urot = nullptr;
   const WinRun* d_wruns = nullptr;  // in the tile allocation (depends on the launch shape)
+  const WinRun* d_fruns = nullptr;
   uint64_t tile_gen = 0;            // bumped whenever the tile tables are rebuilt on the device
   const int32_t* d_dr_cell = nullptr;
   const int64_t* d_dr_ptr = nullptr;
@@ -602,6 +613,14 @@ void build_tiles(Plan& plan, const hbc_tune& t);
 hbc_tune default_tune(const Plan& plan);
 int plane_adjoint_lanes(const Plan& plan);
 bool windows_possible(const Plan& plan);
+// rows of a length that 16-byte vectors do not divide, with no vector
+// components to rotate and no data rows (whose gather assumes whole vectors)
+bool unaligned_rows(const Plan& plan);
+inline int64_t row_vectors(const Plan& plan) {  // 16-byte vectors of a row, the last one whole
+  const int64_t v = plan.dtype == HBC_F64 ? 2 : 4;
+  return (plan.layout.inner + v - 1) / v;
+}
+inline int win_fixed_rows(const Plan& plan) { return row_vectors(plan) <= 64 ? WIN_FIXED_ROWS : WIN_FIXED_LONG_ROWS; }
 void build_csc(Plan& plan);
 void compute_stencil_info(Plan& plan);
 // new values for sub-vector sub_id: recomputes the b values it contributes

@@ -571,19 +571,18 @@ __device__ __forceinline__ double rdl(double v, int k) {
 // Ordered form: the rows' destinations and weights, then the run's source
 // rows, then the rows one after another.  The autotuner picks it where it is
 // faster (at some run lengths it is, in FP32).
-template <typename T, int V, bool NT, int RM>
-__device__ __forceinline__ void win_ordered(const PlanDesc& d, const WinRun* __restrict__ runs, int nitems,
-                                            int nslices, int zero_only, int b) {
+template <typename T, int V, int RM, bool UA>
+__device__ __forceinline__ void win_ordered(const PlanDesc& d, const WinRun* __restrict__ runs, int nslices,
+                                            int zero_only, int item) {
   const int lane = (int)threadIdx.x & 63;
-  const int item = b * 4 + ((int)threadIdx.x >> 6);
-  if (item >= nitems) return;
   const int ri = item / nslices, slc = item - ri * nslices;
   const WinRun rn = runs[ri];
   T* __restrict__ f = static_cast<T*>(d.field);
-  const int64_t nvec = d.inner / V;
+  const int64_t nvec = UA ? (d.inner + V - 1) / V : d.inner / V;
   const int64_t vi = (int64_t)slc * 64 + lane;
   const bool ok = vi < nvec;
-  const int64_t l = (ok ? vi : 0) * V;  // lanes past the row's end repeat vector 0 and store nothing
+  // lanes past the row's end repeat vector 0 and store nothing; UA: the last vector ends at the row's end
+  const int64_t l = UA ? min((ok ? vi : 0) * V, d.inner - V) : (ok ? vi : 0) * V;
   T sign = T(1);
   const int64_t sl = rot_slot<T>(d, rn.rot, l, sign);
   const int R = rn.nrows;
@@ -601,7 +600,7 @@ __device__ __forceinline__ void win_ordered(const PlanDesc& d, const WinRun* __r
     for (int i = 0; i < V; ++i) z.v[i] = T(0);
 #pragma unroll
     for (int r = 0; r < RM; ++r)
-      if (r < R && ok) stv<T, V, NT>(f + (int64_t)rdl(my_dst, r) * d.cs + l, z);
+      if (r < R && ok) stv<T, V, true, UA>(f + (int64_t)rdl(my_dst, r) * d.cs + l, z);
     return;
   }
   const int64_t step = (int64_t)rn.dl * d.cs;
@@ -609,7 +608,7 @@ __device__ __forceinline__ void win_ordered(const PlanDesc& d, const WinRun* __r
   Pack<T, V> x[RM + 3];
 #pragma unroll
   for (int j = 0; j < RM + 3; ++j)
-    if (j < R + 3) x[j] = ldv<T, V>(x0 + (int64_t)j * step);
+    if (j < R + 3) x[j] = ldv<T, V, UA>(x0 + (int64_t)j * step);
   const T* __restrict__ bt = static_cast<const T*>(d.bval) + rn.brow;
 #pragma unroll
   for (int r = 0; r < RM; ++r) {
@@ -629,7 +628,7 @@ __device__ __forceinline__ void win_ordered(const PlanDesc& d, const WinRun* __r
 #pragma unroll
         for (int i = 0; i < V; ++i) y.v[i] = y.v[i] + (rn.b_inner == 1 ? bp[0] : bp[l + i]);
       }
-      if (ok) stv<T, V, NT>(f + (int64_t)rdl(my_dst, r) * d.cs + l, y);
+      if (ok) stv<T, V, true, UA>(f + (int64_t)rdl(my_dst, r) * d.cs + l, y);
     }
   }
 }
@@ -637,21 +636,18 @@ __device__ __forceinline__ void win_ordered(const PlanDesc& d, const WinRun* __r
 // Pipelined form: scalar run descriptor; the rows' destinations and weights,
 // the run's source rows and its b values in flight together; every store
 // issued (see below) so that each row waits only for its own loads.
-template <typename T, int V, bool NT, int RM, bool HB>
-__device__ __forceinline__ void win_pipelined(const PlanDesc& d, const WinRun* __restrict__ runs, int nitems,
-                                              int nslices, int zero_only, int b) {
+template <typename T, int V, int RM, bool HB, bool UA>
+__device__ __forceinline__ void win_pipelined(const PlanDesc& d, const WinRun* __restrict__ runs, int nslices,
+                                              int zero_only, int item) {
   const int lane = (int)threadIdx.x & 63;
-  // the wave's item is the same in every lane: the run descriptor comes
-  // through scalar loads
-  const int item = __builtin_amdgcn_readfirstlane(b * 4 + ((int)threadIdx.x >> 6));
-  if (item >= nitems) return;
   const int ri = item / nslices, slc = item - ri * nslices;
   const WinRun rn = runs[ri];
   T* __restrict__ f = static_cast<T*>(d.field);
-  const int64_t nvec = d.inner / V;
+  const int64_t nvec = UA ? (d.inner + V - 1) / V : d.inner / V;
   const int64_t vi = (int64_t)slc * 64 + lane;
   const bool ok = vi < nvec;
-  const int64_t l = (ok ? vi : 0) * V;  // lanes past the row's end repeat vector 0 and store nothing
+  // lanes past the row's end repeat vector 0 and store nothing; UA: the last vector ends at the row's end
+  const int64_t l = UA ? min((ok ? vi : 0) * V, d.inner - V) : (ok ? vi : 0) * V;
   T sign = T(1);
   const int64_t sl = rot_slot<T>(d, rn.rot, l, sign);
   const int R = rn.nrows;
@@ -665,7 +661,7 @@ __device__ __forceinline__ void win_pipelined(const PlanDesc& d, const WinRun* _
     for (int i = 0; i < V; ++i) z.v[i] = T(0);
 #pragma unroll
     for (int r = 0; r < RM; ++r)
-      if (r < R && ok) stv<T, V, NT>(f + (int64_t)rdl(my_dst, r) * d.cs + l, z);
+      if (r < R && ok) stv<T, V, true, UA>(f + (int64_t)rdl(my_dst, r) * d.cs + l, z);
     return;
   }
   // the rows' destinations and weights, then the run's source rows, all in
@@ -693,7 +689,7 @@ __device__ __forceinline__ void win_pipelined(const PlanDesc& d, const WinRun* _
   const T* x0 = f + (int64_t)rn.src0 * d.cs + sl;
   Pack<T, V> x[RM + 3];
 #pragma unroll
-  for (int j = 0; j < RM + 3; ++j) x[j] = ldv<T, V>(x0 + (int64_t)min(j, R + 2) * step);
+  for (int j = 0; j < RM + 3; ++j) x[j] = ldv<T, V, UA>(x0 + (int64_t)min(j, R + 2) * step);
   __builtin_amdgcn_s_setprio(0);
   auto row_value = [&](int r) {
     const T c0 = rdl(my_w[0], r), c1 = rdl(my_w[1], r), c2 = rdl(my_w[2], r), c3 = rdl(my_w[3], r);
@@ -722,7 +718,7 @@ __device__ __forceinline__ void win_pipelined(const PlanDesc& d, const WinRun* _
 #pragma unroll
         for (int i = 0; i < V; ++i) bv[r].v[i] = b0;
       } else {
-        bv[r] = ldv<T, V>(bp + l);
+        bv[r] = ldv<T, V, UA>(bp + l);
       }
     }
   }
@@ -739,14 +735,106 @@ __device__ __forceinline__ void win_pipelined(const PlanDesc& d, const WinRun* _
     }
     const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc(
         f + (int64_t)rdl(my_dst, min(r, R - 1)) * d.cs, 0, row_bytes, BUF_RSRC_WORD3);
-    stv_buf<T, V, NT>(y, dr, r < R ? off : BUF_OOB);
+    stv_buf<T, V, true>(y, dr, r < R ? off : BUF_OOB);
   }
 }
 
-template <typename T, int V, bool NT, int RM, bool ORD, bool HB>
+// Lane R's value of each 16 lanes, R a constant (a DPP row broadcast: no LDS).
+template <int R>
+__device__ __forceinline__ int bc16(int v) {
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + R, 0xf, 0xf, true);
+}
+template <int R>
+__device__ __forceinline__ float bc16(float v) {
+  return __int_as_float(bc16<R>(__float_as_int(v)));
+}
+template <int R>
+__device__ __forceinline__ double bc16(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)bc16<R>((int)(b & 0xffffffffll));
+  return __longlong_as_double(((long long)bc16<R>((int)(b >> 32)) << 32) | lo);
+}
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// Short rows (at most 32 vectors): a wavefront takes 2 or 4 runs, 1 << gshift
+// lanes each, where the full-wave form would leave most of its lanes without a
+// vector.  Lane k of every 16 holds row k's destination and weights (row R - 1's
+// past the run).  As in the pipelined form every load precedes the first store
+// and nothing is guarded: rows past the run store row R - 1 again, lanes past
+// the row repeat its last vector and groups past the last run repeat that run
+// (the same values to the same places).
+template <typename T, int V, int RM, bool HB, bool UA>
+__device__ __forceinline__ void win_short(const PlanDesc& d, const WinRun* __restrict__ runs, int nruns, int gshift,
+                                          int zero_only, int first) {
+  const int lane = (int)threadIdx.x & 63;
+  const WinRun rn = runs[min(first + (lane >> gshift), nruns - 1)];
+  T* __restrict__ f = static_cast<T*>(d.field);
+  const int nvec = (int)(UA ? (d.inner + V - 1) / V : d.inner / V);
+  const int vi = min(lane & ((1 << gshift) - 1), nvec - 1);
+  const int64_t l = UA ? min((int64_t)vi * V, d.inner - V) : (int64_t)vi * V;
+  T sign = T(1);
+  const int64_t sl = UA ? l : rot_slot<T>(d, rn.rot, l, sign);  // (UA: no components to rotate)
+  const int R = rn.nrows, mr = min(lane & 15, R - 1);
+  const int my_dst = d.row_dst[rn.row_begin + mr];
+  if (zero_only) {
+    Pack<T, V> z;
+#pragma unroll
+    for (int i = 0; i < V; ++i) z.v[i] = T(0);
+    static_for<RM>([&](auto rc) { stv<T, V, true, UA>(f + (int64_t)bc16<rc.value>(my_dst) * d.cs + l, z); });
+    return;
+  }
+  const Pack<T, 4> my_w = ldv<T, 4, true>(static_cast<const T*>(d.ell_val) + rn.tab + 4 * mr);
+  const int64_t step = (int64_t)rn.dl * d.cs;
+  const T* x0 = f + (int64_t)rn.src0 * d.cs + sl;
+  Pack<T, V> x[RM + 3];
+#pragma unroll
+  for (int j = 0; j < RM + 3; ++j) x[j] = ldv<T, V, UA>(x0 + (int64_t)min(j, R + 2) * step);
+  Pack<T, V> bv[HB ? RM : 1];
+  if (HB && rn.has_b) {
+    const T* __restrict__ bt = static_cast<const T*>(d.bval) + rn.brow;
+#pragma unroll
+    for (int r = 0; r < RM; ++r) {
+      const T* bp = bt + (int64_t)min(r, R - 1) * rn.b_inner;
+      if (rn.b_inner == 1) {
+        const T b0 = bp[0];
+#pragma unroll
+        for (int i = 0; i < V; ++i) bv[r].v[i] = b0;
+      } else {
+        bv[r] = ldv<T, V, UA>(bp + l);
+      }
+    }
+  }
+  Pack<T, V> y;
+  static_for<RM>([&](auto rc) {
+    constexpr int r = rc.value;
+    const T c0 = bc16<r>(my_w.v[0]), c1 = bc16<r>(my_w.v[1]), c2 = bc16<r>(my_w.v[2]), c3 = bc16<r>(my_w.v[3]);
+    const bool live = r == 0 || r < R;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      T a = c0 * x[r].v[i];
+      a = fma(c1, x[r + 1].v[i], a);
+      a = fma(c2, x[r + 2].v[i], a);
+      a = fma(c3, x[r + 3].v[i], a);
+      a = sign * a;
+      if constexpr (HB) a = rn.has_b ? a + bv[r].v[i] : a;
+      y.v[i] = live ? a : y.v[i];
+    }
+    stv<T, V, true, UA>(f + (int64_t)bc16<r>(my_dst) * d.cs + l, y);
+  });
+}
+
+// FORM: WIN_PIPELINED, WIN_ORDERED or WIN_SHORT (gshift: log2 lanes per run).
+enum { WIN_PIPELINED = 0, WIN_ORDERED = 1, WIN_SHORT = 2 };
+template <typename T, int V, int RM, int FORM, bool HB, bool UA>
 __global__ __launch_bounds__(256) void k_apply_win(PlanDesc d, const WinRun* __restrict__ runs, int nitems,
                                                    int nslices, int zero_only, const RowTile* __restrict__ ztiles,
-                                                   int nz) {
+                                                   int nz, int gshift) {
   const int nwin = (nitems + 3) >> 2;
   if ((int)blockIdx.x >= nwin) {
     for (int t = (int)blockIdx.x - nwin; t < nz; t += (int)gridDim.x - nwin) zero_row_tile<T>(d, ztiles[t]);
@@ -759,10 +847,16 @@ __global__ __launch_bounds__(256) void k_apply_win(PlanDesc d, const WinRun* __r
     const int q = nwin >> 3, rem = nwin & 7, x = b & 7, jx = b >> 3;
     b = x * q + min(x, rem) + jx;
   }
-  if constexpr (ORD)
-    win_ordered<T, V, NT, RM>(d, runs, nitems, nslices, zero_only, b);
+  // the wave's item is the same in every lane: the run descriptor comes
+  // through scalar loads (the full-wave forms)
+  const int item = __builtin_amdgcn_readfirstlane(b * 4 + ((int)threadIdx.x >> 6));
+  if (item >= nitems) return;
+  if constexpr (FORM == WIN_SHORT)
+    win_short<T, V, RM, HB, UA>(d, runs, nslices, gshift, zero_only, item << (6 - gshift));  // nslices: runs
+  else if constexpr (FORM == WIN_ORDERED)
+    win_ordered<T, V, RM, UA>(d, runs, nslices, zero_only, item);
   else
-    win_pipelined<T, V, NT, RM, HB>(d, runs, nitems, nslices, zero_only, b);
+    win_pipelined<T, V, RM, HB, UA>(d, runs, nslices, zero_only, item);
 }
 
 // One entry of a wide tile: its weight and the LDS offset (in values) of its
@@ -2422,6 +2516,10 @@ int ilog2(int v) {
   return s;
 }
 
+// log2 lanes per run of the window kernel: 16 or 32 lanes where a row's
+// vectors fit them, else whole wavefronts.
+int win_short_shift(int64_t nvec) { return nvec <= 16 ? 4 : nvec <= 32 ? 5 : 6; }
+
 PlanDesc make_desc(const Plan& p, void* field) {
   PlanDesc d{};
   d.field = field;
@@ -2453,11 +2551,7 @@ PlanDesc make_desc(const Plan& p, void* field) {
   d.general = 0;
   for (const RowTile& t : p.host.rtiles)
     if (t.kind == SEG_CSR || (t.kind == SEG_ELL && (t.width != 4 || (t.flags & SEGF_ELL_PADDED)))) d.general = 1;
-  // rows of a length that 16-byte vectors do not divide, with no vector
-  // components to rotate and no data rows (whose gather assumes whole vectors)
-  const int64_t vfull = p.dtype == HBC_F64 ? 2 : 4;
-  d.ua = p.layout.order == HBC_POINT_MAJOR && p.layout.vec_len == 0 && p.stats.rows_data == 0 &&
-         p.layout.inner % vfull != 0 && p.layout.inner > vfull;
+  d.ua = unaligned_rows(p);
   return d;
 }
 
@@ -2510,6 +2604,7 @@ void device_upload_plan(Plan& p) {
   size_t o_wp = pk.vec(T.w_rp);
   size_t o_we = pk.wide_entries(T.w_entw, T.w_ents, p.dtype, wide_slice_bytes(p) / (p.dtype == HBC_F64 ? 8 : 4));
   size_t o_nt = pk.vec(T.ntiles);
+  size_t o_fr = pk.vec(T.fruns);
   size_t o_pp = pk.vec(T.p_pieces), o_pd = pk.vec(T.p_dst), o_pm = pk.vec(T.p_meta), o_pb = pk.vec(T.p_brow),
          o_pc = pk.vec(T.p_col), o_ps = pk.vec(T.p_slot), o_pw = pk.reals(T.p_w, p.dtype), o_pu = pk.vec(T.p_ucell),
          o_pr = pk.vec(T.p_urot);
@@ -2545,6 +2640,7 @@ void device_upload_plan(Plan& p) {
   p.d_w_rp = reinterpret_cast<const int32_t*>(b + o_wp);
   p.d_w_ent = b + o_we;
   p.d_ntiles = reinterpret_cast<const NarrowTile*>(b + o_nt);
+  p.d_fruns = reinterpret_cast<const WinRun*>(b + o_fr);
   p.d_p_dst = reinterpret_cast<const int32_t*>(b + o_pd);
   p.d_p_meta = reinterpret_cast<const int32_t*>(b + o_pm);
   p.d_p_brow = reinterpret_cast<const int64_t*>(b + o_pb);
@@ -2794,54 +2890,81 @@ static void launch_wide(const Plan& p, const PlanDesc& d, hipStream_t st, bool z
   HIP_CHECK(hipGetLastError());
 }
 
-// Sliding-window runs: one wavefront per (run, slice of 64 vectors), four
-// per workgroup; nz zero-row tiles ride in extra workgroups.
-template <typename T>
-static void launch_win(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only, int nz) {
-  constexpr int V = 16 / (int)sizeof(T);
-  const int64_t nvec = p.layout.inner / V;
-  const int64_t nsl = (nvec + 63) / 64;
-  const int64_t nitems = (int64_t)p.host.wruns.size() * nsl;
+// Sliding-window runs: one wavefront per (run, slice of 64 vectors), or per 2
+// or 4 runs of at most 32 or 16 vectors; four wavefronts per workgroup; nz
+// zero-row tiles ride in extra workgroups.
+template <typename T, int RM, int FORM, bool HB, bool UA>
+static void launch_runs(const Plan& p, const PlanDesc& d, hipStream_t st, const WinRun* runs, size_t nruns, int z,
+                        int nz) {
+  const int64_t nvec = row_vectors(p), nsl = (nvec + 63) / 64;
+  const int gshift = win_short_shift(nvec);
+  const int64_t nitems = FORM == WIN_SHORT ? ((int64_t)nruns + (64 >> gshift) - 1) >> (6 - gshift) : (int64_t)nruns * nsl;
   if (nitems >= (int64_t(1) << 30)) fail(HBC_EUNSUPPORTED, "too many window runs for one launch");
   const int nwin = (int)((nitems + 3) / 4);
-  const dim3 g((unsigned)(nwin + nz)), b(256);
-  const int z = zero_only ? 1 : 0;
-  const int rm = p.host.win_maxr;  // longest run: the smallest instance that holds it
-#define HBC_WIN_O(RM, O, HB)                                                                                      \
-  do {                                                                                                              \
-    if (d.nt)                                                                                                       \
-      HBC_LAUNCH((k_apply_win<T, V, true, RM, O, HB>), g, b, 0, st, d, p.d_wruns, (int)nitems, (int)nsl, z,  \
-                         p.d_rtiles, nz);                                                                          \
-    else                                                                                                            \
-      HBC_LAUNCH((k_apply_win<T, V, false, RM, O, HB>), g, b, 0, st, d, p.d_wruns, (int)nitems, (int)nsl, z, \
-                         p.d_rtiles, nz);                                                                          \
-  } while (0)
-#define HBC_WIN(RM)                         \
-  do {                                      \
-    if (p.tune.window_order)                \
-      HBC_WIN_O(RM, true, false);           \
-    else if (p.host.win_has_b)              \
-      HBC_WIN_O(RM, false, true);           \
-    else                                    \
-      HBC_WIN_O(RM, false, false);          \
-  } while (0)
-  // one instance per run length the autotuner tries: every load slot of a
-  // full run is used (a shorter run re-reads its last source row)
-  if (rm <= 4)
-    HBC_WIN(4);
-  else if (rm <= 6)
-    HBC_WIN(6);
-  else if (rm <= 8)
-    HBC_WIN(8);
-  else if (rm <= 10)
-    HBC_WIN(10);
-  else if (rm <= 12)
-    HBC_WIN(12);
-  else
-    HBC_WIN(16);
-#undef HBC_WIN
-#undef HBC_WIN_O
+  HBC_LAUNCH((k_apply_win<T, 16 / (int)sizeof(T), RM, FORM, HB, UA>), dim3((unsigned)(nwin + nz)), dim3(256), 0, st, d,
+             runs, (int)nitems, (int)(FORM == WIN_SHORT ? (int64_t)nruns : nsl), z, p.d_rtiles, nz, gshift);
   HIP_CHECK(hipGetLastError());
+}
+
+// Runs of the tuned length: one instance per run length the autotuner tries
+// (every load slot of a full run is used; a shorter run re-reads its last
+// source row).
+template <typename T, int RM>
+static void launch_win_rm(const Plan& p, const PlanDesc& d, hipStream_t st, int z, int nz) {
+  const size_t n = p.host.wruns.size();
+  const bool shrt = win_short_shift(row_vectors(p)) < 6;
+  if (shrt && p.host.win_has_b)
+    launch_runs<T, RM, WIN_SHORT, true, false>(p, d, st, p.d_wruns, n, z, nz);
+  else if (shrt)
+    launch_runs<T, RM, WIN_SHORT, false, false>(p, d, st, p.d_wruns, n, z, nz);
+  else if (p.tune.window_order)
+    launch_runs<T, RM, WIN_ORDERED, false, false>(p, d, st, p.d_wruns, n, z, nz);
+  else if (p.host.win_has_b)
+    launch_runs<T, RM, WIN_PIPELINED, true, false>(p, d, st, p.d_wruns, n, z, nz);
+  else
+    launch_runs<T, RM, WIN_PIPELINED, false, false>(p, d, st, p.d_wruns, n, z, nz);
+}
+
+template <typename T>
+static void launch_win(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only, int nz) {
+  const int rm = p.host.win_maxr, z = zero_only ? 1 : 0;  // longest run: the smallest instance that holds it
+  if (rm <= 4)
+    launch_win_rm<T, 4>(p, d, st, z, nz);
+  else if (rm <= 6)
+    launch_win_rm<T, 6>(p, d, st, z, nz);
+  else if (rm <= 8)
+    launch_win_rm<T, 8>(p, d, st, z, nz);
+  else if (rm <= 10)
+    launch_win_rm<T, 10>(p, d, st, z, nz);
+  else if (rm <= 12)
+    launch_win_rm<T, 12>(p, d, st, z, nz);
+  else
+    launch_win_rm<T, 16>(p, d, st, z, nz);
+}
+
+// Runs of a fixed length (see WIN_FIXED_BYTES).  Rows of whole vectors are
+// short ones here (longer ones take the tuned runs).
+template <typename T, bool HB>
+static void launch_fixed_hb(const Plan& p, const PlanDesc& d, hipStream_t st, int z, int nz) {
+  const size_t n = p.host.fruns.size();
+  const bool shrt = win_short_shift(row_vectors(p)) < 6;
+  if (!d.ua)
+    launch_runs<T, WIN_FIXED_ROWS, WIN_SHORT, HB, false>(p, d, st, p.d_fruns, n, z, nz);
+  else if (shrt)
+    launch_runs<T, WIN_FIXED_ROWS, WIN_SHORT, HB, true>(p, d, st, p.d_fruns, n, z, nz);
+  else if (win_fixed_rows(p) == WIN_FIXED_ROWS)
+    launch_runs<T, WIN_FIXED_ROWS, WIN_PIPELINED, HB, true>(p, d, st, p.d_fruns, n, z, nz);
+  else
+    launch_runs<T, WIN_FIXED_LONG_ROWS, WIN_PIPELINED, HB, true>(p, d, st, p.d_fruns, n, z, nz);
+}
+
+template <typename T>
+static void launch_fixed(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only, int nz) {
+  const int z = zero_only ? 1 : 0;
+  if (p.host.fix_has_b)
+    launch_fixed_hb<T, true>(p, d, st, z, nz);
+  else
+    launch_fixed_hb<T, false>(p, d, st, z, nz);
 }
 
 // Plane-major plans: the rows of few entries, then the tiles of the others.
@@ -2893,8 +3016,8 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
   // fold the row tiles into the first wide-row or window launch when they are
   // all zero rows without b (the corners of the cubed-sphere programs)
   const bool has_narrow = pm && !p.host.ntiles.empty(), has_wide = pm && !p.host.wtiles.empty();
-  const bool has_win = pm && !p.host.wruns.empty();
-  bool fold = (has_narrow || has_wide || has_win) && dd.grid == 0 && nt > 0;
+  const bool has_win = pm && !p.host.wruns.empty(), has_fixed = pm && !p.host.fruns.empty();
+  bool fold = (has_narrow || has_wide || has_win || has_fixed) && dd.grid == 0 && nt > 0;
   for (size_t k = 0; fold && k < p.host.rtiles.size(); ++k)
     fold = p.host.rtiles[k].kind == SEG_ZERO && !p.host.rtiles[k].has_b;
   if (has_narrow) {
@@ -2922,6 +3045,7 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
     }
   }
   if (has_win) launch_win<T>(p, d, st, zero_only, fold && !has_narrow && !has_wide ? nt : 0);
+  if (has_fixed) launch_fixed<T>(p, d, st, zero_only, fold && !has_narrow && !has_wide && !has_win ? nt : 0);
   if (!pm) {
     launch_planes<T>(p, d, st, z);
     return;

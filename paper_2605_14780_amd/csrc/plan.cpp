@@ -781,6 +781,13 @@ static bool win_seg_shape(const Plan& plan, const DevSeg& sg) {
   return !(sg.has_b && plan.layout.inner * es < WIN_MIN_BYTES_B);
 }
 
+bool unaligned_rows(const Plan& plan) {
+  const Layout& L = plan.layout;
+  const int64_t vfull = plan.dtype == HBC_F64 ? 2 : 4;
+  return L.order == HBC_POINT_MAJOR && L.vec_len == 0 && plan.stats.rows_data == 0 && L.inner % vfull != 0 &&
+         L.inner > vfull;
+}
+
 // Whether build_windows can take a segment of the plan (its column patterns
 // aside): point-major, whole 16-byte vectors, rows of >= WIN_MIN_BYTES, a
 // segment of the window shape.
@@ -1113,62 +1120,93 @@ static void build_planes(Plan& plan) {
   close();
 }
 
-// Sliding-window runs (see WinRun).  A segment qualifies when every row is a
-// window (four cells c, c + dl, c + 2 dl, c + 3 dl, dl != 0).  Its rows are
-// cut, in device order, into runs of at most rmax rows in which each row's
-// window starts one cell further along the same line than the previous
-// row's; a new run starts where that fails (at the next ghost layer of a
-// strip, or where two neighbouring ghosts share a stencil).  Rows of other
-// segments keep the row tiles.
+// Whether the other window-shaped segments of a plan go in runs of a fixed
+// length: rows of at least WIN_FIXED_BYTES in 16-byte vectors (on element
+// boundaries where they do not divide the row).
+static bool fixed_windows(const Plan& plan) {
+  const Layout& L = plan.layout;
+  const int64_t es = plan.dtype == HBC_F64 ? 8 : 4;
+  if (L.order != HBC_POINT_MAJOR || (plan.flags & HBC_PLAN_NO_WINDOWS) || plan.stats.rows_data > 0) return false;
+  return (plan.vec * es == 16 || unaligned_rows(plan)) && L.inner * es >= WIN_FIXED_BYTES &&
+         L.inner * es < (int64_t(1) << 31);
+}
+
+// Whether every row of a 4-wide ELL segment is a window: four cells c, c + dl,
+// c + 2 dl, c + 3 dl, dl != 0.
+static bool window_rows(const HostTables& T, const DevSeg& sg) {
+  if (sg.kind != SEG_ELL || sg.width != 4 || (sg.flags & SEGF_ELL_PADDED) || sg.nrows == 0) return false;
+  const int32_t* c = T.ell_col.data() + sg.tab;
+  for (int64_t r = 0; r < sg.nrows; ++r, c += 4) {
+    const int64_t dl = (int64_t)c[1] - c[0];
+    if (dl == 0 || dl <= INT32_MIN || dl >= INT32_MAX) return false;
+    for (int m = 2; m < 4; ++m)
+      if ((int64_t)c[m] - c[0] != m * dl) return false;
+  }
+  return true;
+}
+
+// The runs of such a segment, in device order: at most `most` rows in which
+// each row's window starts one cell further along the same line than the
+// previous row's; a new run starts where that fails (at the next ghost layer
+// of a strip, or where two neighbouring ghosts share a stencil).  Returns the
+// longest run.
+static int32_t cut_runs(const HostTables& T, const DevSeg& sg, int most, std::vector<WinRun>& out) {
+  const int32_t* c = T.ell_col.data() + sg.tab;
+  auto dl_of = [&](int64_t r) { return (int64_t)c[4 * r + 1] - c[4 * r]; };
+  int64_t r0 = 0, longest = 0;
+  while (r0 < sg.nrows) {
+    const int64_t dl = dl_of(r0);
+    int64_t n = 1;
+    while (r0 + n < sg.nrows && n < most) {
+      const int64_t r = r0 + n;
+      if (dl_of(r) != dl || (int64_t)c[4 * r] - c[4 * (r - 1)] != dl) break;
+      ++n;
+    }
+    WinRun w{};
+    w.src0 = c[4 * r0];
+    w.dl = (int32_t)dl;
+    w.nrows = (int32_t)n;
+    w.nsrc = (int32_t)(n + 3);
+    w.row_begin = sg.row_base + r0;
+    w.tab = sg.tab + 4 * r0;
+    w.brow = sg.brow + r0 * sg.b_inner;
+    w.rot = sg.rot;
+    w.has_b = sg.has_b;
+    w.b_inner = sg.b_inner;
+    out.push_back(w);
+    longest = std::max(longest, n);
+    r0 += n;
+  }
+  return (int32_t)longest;
+}
+
+// Sliding-window runs (see WinRun) of the segments of window rows: of at most
+// rmax rows, or WIN_FIXED_ROWS for the segments of fixed_windows.  Rows of
+// other segments keep the row tiles.
 static void build_windows(Plan& plan, int rmax) {
   HostTables& T = plan.host;
   T.seg_win.assign(T.segs.size(), 0);
   T.wruns.clear();
+  T.fruns.clear();
   T.win_maxr = 0;
-  T.win_has_b = false;
+  T.win_has_b = T.fix_has_b = false;
   plan.stats.rows_window = plan.stats.window_runs = 0;
-  if (!windows_possible(plan)) return;
+  const bool tuned = windows_possible(plan), fixed = fixed_windows(plan);
+  if (!tuned && !fixed) return;
   rmax = std::max(1, std::min(rmax, WIN_MAXR));
   for (size_t si = 0; si < T.segs.size(); ++si) {
     const DevSeg& sg = T.segs[si];
-    if (!win_seg_shape(plan, sg)) continue;
-    if (T.seg_wide.size() == T.segs.size() && T.seg_wide[si]) continue;
-    const int32_t* c = T.ell_col.data() + sg.tab;
-    auto dl_of = [&](int64_t r) { return (int64_t)c[4 * r + 1] - c[4 * r]; };
-    bool ok = true;
-    for (int64_t r = 0; r < sg.nrows && ok; ++r) {
-      const int64_t dl = dl_of(r);
-      ok = dl != 0 && dl > INT32_MIN && dl < INT32_MAX;
-      for (int m = 2; m < 4 && ok; ++m) ok = (int64_t)c[4 * r + m] - c[4 * r] == m * dl;
-    }
-    if (!ok) continue;
+    const bool own = tuned && win_seg_shape(plan, sg);
+    if ((!own && !fixed) || !window_rows(T, sg)) continue;
     T.seg_win[si] = 1;
-    int64_t r0 = 0;
-    while (r0 < sg.nrows) {
-      const int64_t dl = dl_of(r0);
-      int64_t n = 1;
-      while (r0 + n < sg.nrows && n < rmax) {
-        const int64_t r = r0 + n;
-        if (dl_of(r) != dl || (int64_t)c[4 * r] - c[4 * (r - 1)] != dl) break;
-        ++n;
-      }
-      WinRun w{};
-      w.src0 = c[4 * r0];
-      w.dl = (int32_t)dl;
-      w.nrows = (int32_t)n;
-      w.nsrc = (int32_t)(n + 3);
-      w.row_begin = sg.row_base + r0;
-      w.tab = sg.tab + 4 * r0;
-      w.brow = sg.brow + r0 * sg.b_inner;
-      w.rot = sg.rot;
-      w.has_b = sg.has_b;
-      w.b_inner = sg.b_inner;
-      T.wruns.push_back(w);
-      T.win_maxr = std::max<int32_t>(T.win_maxr, (int32_t)n);
+    if (own) {
+      T.win_maxr = std::max(T.win_maxr, cut_runs(T, sg, rmax, T.wruns));
       T.win_has_b = T.win_has_b || sg.has_b;
-      r0 += n;
+      plan.stats.rows_window += sg.nrows;
+    } else {
+      cut_runs(T, sg, win_fixed_rows(plan), T.fruns);
+      T.fix_has_b = T.fix_has_b || sg.has_b;
     }
-    plan.stats.rows_window += sg.nrows;
   }
   plan.stats.window_runs = (int64_t)T.wruns.size();
 }

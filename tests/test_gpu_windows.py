@@ -126,3 +126,34 @@ def test_window_adjoint_and_graph_after_tuning():
         g2.launch(s.cuda_stream)
         s.synchronize()
         assert torch.equal(f, want)
+
+
+# rows of 8 to 129 vectors around the 16, 32 and 64 lanes a run can take, whole
+# and ending in a part of a vector; from the shortest rows that take runs
+@pytest.mark.parametrize("dtype,inners", [("f64", (16, 17, 32, 33, 34, 63, 64, 65, 66, 127, 129, 131, 257)),
+                                          ("f32", (32, 33, 63, 64, 65, 67, 68, 127, 129, 130, 255, 259, 513))])
+@pytest.mark.parametrize("b", [None, 1, "inner"])
+def test_short_and_unaligned_windows_bitwise_general_path(dtype, inners, b):
+    """Rows shorter than a wavefront's slice (several runs per wavefront) and
+    rows of a length that vectors do not divide, with and without b, give the
+    general path's bits, also where N leaves the last run and the last group
+    of runs short."""
+    dt, tdt = (hb.F64, torch.float64) if dtype == "f64" else (hb.F32, torch.float32)
+    for N, h in ((7, 1), (24, 2)):
+        _, prog = hb.cs_program(N, h, hb.CS_LAGRANGE)
+        for inner in inners:
+            p = hb.cs_program(N, h, hb.CS_LAGRANGE)[1] if b else prog
+            rng = np.random.default_rng(inner)
+            if b:
+                n = inner if b == "inner" else 1
+                for f in (0, 3):
+                    p.add_vector([(f, f + 1), (0, N), (-h, 0)], rng.normal(size=N * h * n), ninner=n)
+            pw = hb.Plan(p, inner=inner, dtype=dt)
+            pr = hb.Plan(p, inner=inner, dtype=dt, windows=False)
+            assert any("k_apply_win" in k for k in pw.kernels())
+            x = torch.from_numpy(rng.normal(size=(p.grid.cells, inner))).to(tdt).cuda()
+            want, got = x.clone(), x.clone()
+            hb.apply(pr, want)
+            hb.apply(pw, got)
+            torch.cuda.synchronize()
+            assert torch.equal(got, want), (N, inner)
