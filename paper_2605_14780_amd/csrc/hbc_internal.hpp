@@ -134,7 +134,8 @@ int rot_inverse(int code);
 void rot_matrix(int code, int32_t* R);
 
 // ---- device-facing tables ---------------------------------------------------
-enum SegKind { SEG_ZERO = 0, SEG_MAP = 1, SEG_ELL = 2, SEG_CSR = 3, SEG_VEC = 4, SEG_DATA_ROW = 5 };
+// (SEG_RUNS: a batch tile of sliding-window runs, no segment's own kind)
+enum SegKind { SEG_ZERO = 0, SEG_MAP = 1, SEG_ELL = 2, SEG_CSR = 3, SEG_VEC = 4, SEG_DATA_ROW = 5, SEG_RUNS = 6 };
 constexpr int SEG_MAXD = 4;
 
 struct alignas(16) DevSeg {
@@ -621,6 +622,8 @@ inline int64_t row_vectors(const Plan& plan) {  // 16-byte vectors of a row, the
   return (plan.layout.inner + v - 1) / v;
 }
 inline int win_fixed_rows(const Plan& plan) { return row_vectors(plan) <= 64 ? WIN_FIXED_ROWS : WIN_FIXED_LONG_ROWS; }
+// runs of fixed length of the plan's window segments without b, for a batch (whatever the plan's tune)
+void batch_windows(const Plan& plan, std::vector<char>& seg_win, std::vector<WinRun>& runs);
 void build_csc(Plan& plan);
 void compute_stencil_info(Plan& plan);
 // new values for sub-vector sub_id: recomputes the b values it contributes

@@ -1411,12 +1411,41 @@ __device__ __forceinline__ void rt_tile_any(const PlanDesc& d, const RowTile& tl
   }
 }
 
+// A batch tile of window runs: its wavefronts take the plan's items tl.tab,
+// tl.tab + 1, ... of tl.brow runs at runs[tl.row_begin] (a run and a slice, or
+// 2 or 4 runs of short rows).
+template <typename T, bool UA>
+__device__ __forceinline__ void batch_runs(const PlanDesc& d, const RowTile& tl, const WinRun* __restrict__ runs) {
+  constexpr int V = 16 / (int)sizeof(T);
+  const int nvec = (int)((d.inner + V - 1) / V), nruns = (int)tl.brow;
+  const int item = __builtin_amdgcn_readfirstlane((int)tl.tab + ((int)threadIdx.x >> 6));
+  const WinRun* r = runs + tl.row_begin;
+  if (nvec <= 32) {
+    const int gshift = nvec <= 16 ? 4 : 5, first = item << (6 - gshift);
+    if (first < nruns) win_short<T, V, WIN_FIXED_ROWS, false, UA>(d, r, nruns, gshift, 0, first);
+    return;
+  }
+  const int nsl = (nvec + 63) >> 6;
+  if (item >= nruns * nsl) return;
+  if (nsl == 1)
+    win_pipelined<T, V, WIN_FIXED_ROWS, false, UA>(d, r, 1, 0, item);
+  else
+    win_pipelined<T, V, WIN_FIXED_LONG_ROWS, false, UA>(d, r, nsl, 0, item);
+}
+
 template <typename T, int KM>
 __global__ __launch_bounds__(256) void k_batch(const PlanDesc* __restrict__ descs, const RowTile* __restrict__ tiles,
-                                               int ntiles) {
+                                               int ntiles, const WinRun* __restrict__ runs) {
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const RowTile tl = tiles[t];
     const PlanDesc d = descs[tl.pad_];
+    if (tl.kind == SEG_RUNS) {
+      if (d.ua)
+        batch_runs<T, true>(d, tl, runs);
+      else
+        batch_runs<T, false>(d, tl, runs);
+      continue;
+    }
     if (d.nt)
       rt_tile_any<T, true, KM>(d, tl);
     else
@@ -3602,6 +3631,8 @@ struct Batch {
   PlanDesc* d_descs = nullptr;
   std::vector<RowTile> tiles;
   RowTile* d_tiles = nullptr;
+  WinRun* d_runs = nullptr;  // window runs of every plan
+  bool general = false;      // general ELL/CSR rows among the tiles
   bool bound = false;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -3626,11 +3657,15 @@ static void batch_tiles(Batch* b) {
   // values; rows_per_tile = 0 gives every row group one batch of rows (all
   // loads of a workgroup issued before its first store)
   std::vector<std::vector<RowTile>> per(b->plans.size());
+  std::vector<WinRun> runs, own;
+  std::vector<char> seg_win;
+  b->general = false;
   for (size_t k = 0; k < b->plans.size(); ++k) {
     const Plan& p = *b->plans[k];
     const int64_t I = p.layout.inner;
     int lpr = p.tune.lanes_per_row;
     if (b->tune.lanes_per_row > 0) lpr = std::min(lpr, b->tune.lanes_per_row);
+    while (lpr > b->tune.block) lpr /= 2;  // a row group fits its workgroup (longer rows take more passes)
     b->descs[k].lpr_shift = ilog2(lpr);
     b->descs[k].chunked = lpr >= CHUNK_LPR ? 1 : 0;
     const int64_t rp = std::max<int64_t>(1, b->tune.block / lpr);
@@ -3638,8 +3673,26 @@ static void batch_tiles(Batch* b) {
     rpt = ((rpt + rp - 1) / rp) * rp;
     if (b->tune.rows_per_tile == 0) rpt = rp * batch_rows_per_batch(b->descs[k], b->dtype);
     rpt = std::min<int64_t>(rpt, 1 << 20);
+    batch_windows(p, seg_win, own);
+    const int64_t nvec = row_vectors(p), nsl = (nvec + 63) / 64, nruns = (int64_t)own.size();
+    const int gshift = win_short_shift(nvec), nw = b->tune.block / 64;
+    const int64_t items = gshift < 6 ? (nruns + (64 >> gshift) - 1) >> (6 - gshift) : nruns * nsl;
+    if (items >= (int64_t(1) << 30)) fail(HBC_EUNSUPPORTED, "too many window runs for one launch");
+    for (int64_t i = 0; i < items; i += nw) {
+      RowTile rt{};
+      rt.kind = SEG_RUNS;
+      rt.row_begin = (int64_t)runs.size();
+      rt.tab = i;
+      rt.brow = nruns;
+      rt.pad_ = (int32_t)k;
+      per[k].push_back(rt);
+    }
+    runs.insert(runs.end(), own.begin(), own.end());
     for (size_t s = 0; s < p.host.segs.size(); ++s) {
       const DevSeg& sg = p.host.segs[s];
+      if (seg_win[s]) continue;
+      if (sg.nrows > 0 && (sg.kind == SEG_CSR || (sg.kind == SEG_ELL && (sg.width != 4 || (sg.flags & SEGF_ELL_PADDED)))))
+        b->general = true;
       for (int64_t r0 = 0; r0 < sg.nrows; r0 += rpt) {
         RowTile rt{};
         rt.kind = sg.kind;
@@ -3679,6 +3732,10 @@ static void batch_tiles(Batch* b) {
   HIP_CHECK(hipMalloc(&b->d_tiles, std::max<size_t>(1, b->tiles.size()) * sizeof(RowTile)));
   if (!b->tiles.empty())
     HIP_CHECK(hipMemcpy(b->d_tiles, b->tiles.data(), b->tiles.size() * sizeof(RowTile), hipMemcpyHostToDevice));
+  if (b->d_runs) HIP_CHECK(hipFree(b->d_runs));
+  b->d_runs = nullptr;
+  HIP_CHECK(hipMalloc(&b->d_runs, std::max<size_t>(1, runs.size()) * sizeof(WinRun)));
+  if (!runs.empty()) HIP_CHECK(hipMemcpy(b->d_runs, runs.data(), runs.size() * sizeof(WinRun), hipMemcpyHostToDevice));
   b->stats.tiles = (int64_t)b->tiles.size();
   if (b->bound) device_batch_bind(b, nullptr);
 }
@@ -3711,13 +3768,13 @@ Batch* device_batch_create(Plan* const* plans, int n) {
       b->stats.table_bytes += (int64_t)plans[k]->dev_bytes;
     }
     HIP_CHECK(hipMalloc(&b->d_descs, n * sizeof(PlanDesc)));
-    b->tune.block = 256;
+    // one batch of rows per row group and one workgroup per tile: every
+    // workgroup issues all its loads before its first store (24 FP32 grids:
+    // 64 us against 84 with 1024 workgroups walking tiles of 8192 values)
+    b->tune.block = 128;
     b->tune.lanes_per_row = 0;
-    b->tune.rows_per_tile = 8192;
-    int dev = 0, ncu = 256;
-    HIP_CHECK(hipGetDevice(&dev));
-    HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    b->tune.persistent = 4 * ncu;
+    b->tune.rows_per_tile = 0;
+    b->tune.persistent = 0;
     batch_tiles(b);
   } catch (...) {
     device_batch_destroy(b);
@@ -3732,6 +3789,7 @@ void device_batch_destroy(Batch* b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->d_descs) (void)hipFree(b->d_descs);
   if (b->d_tiles) (void)hipFree(b->d_tiles);
+  if (b->d_runs) (void)hipFree(b->d_runs);
   delete b;
 }
 
@@ -3766,20 +3824,17 @@ void device_batch_apply(Batch* b, void* stream) {
   const int nt = (int)b->tiles.size();
   if (nt == 0) return;
   const int grid = b->tune.persistent > 0 ? std::min(b->tune.persistent, nt) : nt;
-  bool gen = false;  // any general ELL/CSR rows among the tiles
-  for (const RowTile& t : b->tiles)
-    if (t.kind == SEG_CSR || (t.kind == SEG_ELL && (t.width != 4 || (t.flags & SEGF_ELL_PADDED)))) gen = true;
   const dim3 g(grid), blk(b->tune.block);
   if (b->dtype == HBC_F64) {
-    if (gen)
-      hipLaunchKernelGGL((k_batch<double, 3 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt);
+    if (b->general)
+      hipLaunchKernelGGL((k_batch<double, 3 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt, b->d_runs);
     else
-      hipLaunchKernelGGL((k_batch<double, 1 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt);
+      hipLaunchKernelGGL((k_batch<double, 1 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt, b->d_runs);
   } else {
-    if (gen)
-      hipLaunchKernelGGL((k_batch<float, 3 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt);
+    if (b->general)
+      hipLaunchKernelGGL((k_batch<float, 3 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt, b->d_runs);
     else
-      hipLaunchKernelGGL((k_batch<float, 1 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt);
+      hipLaunchKernelGGL((k_batch<float, 1 | KM_SEQFB>), g, blk, 0, S(stream), b->d_descs, b->d_tiles, nt, b->d_runs);
   }
   HIP_CHECK(hipGetLastError());
 }
@@ -3823,7 +3878,8 @@ void device_batch_stats(const Batch* b, hbc_stats* out) { *out = b->stats; }
 // Generation of the kernels' performance, part of every autotune cache key:
 // a choice stored by a build whose kernels time differently is not reused
 // (bumped with such changes; 2: window loads at raised priority, where runs
-// of 4 turned from the fastest to among the slowest; 3: plane-major pieces).
+// of 4 turned from the fastest to among the slowest; 3: plane-major pieces,
+// short windows, windows in batches).
 constexpr int TUNE_CACHE_GEN = 3;
 
 static std::string batch_key(const Batch* b) {

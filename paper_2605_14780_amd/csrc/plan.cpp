@@ -1211,6 +1211,18 @@ static void build_windows(Plan& plan, int rmax) {
   plan.stats.window_runs = (int64_t)T.wruns.size();
 }
 
+void batch_windows(const Plan& plan, std::vector<char>& seg_win, std::vector<WinRun>& runs) {
+  const HostTables& T = plan.host;
+  seg_win.assign(T.segs.size(), 0);
+  runs.clear();
+  if (!fixed_windows(plan)) return;
+  for (size_t si = 0; si < T.segs.size(); ++si) {
+    if (T.segs[si].has_b || !window_rows(T, T.segs[si])) continue;
+    seg_win[si] = 1;
+    cut_runs(T, T.segs[si], win_fixed_rows(plan), runs);
+  }
+}
+
 void build_tiles(Plan& plan, const hbc_tune& t) {
   if (t.block < 64 || t.block > 256 || t.block % 64) fail(HBC_EINVAL, "block must be 64, 128, 192 or 256");
   if (t.lanes_per_row < 1 || (t.lanes_per_row & (t.lanes_per_row - 1)) || t.lanes_per_row > t.block)

@@ -157,3 +157,31 @@ def test_short_and_unaligned_windows_bitwise_general_path(dtype, inners, b):
             hb.apply(pw, got)
             torch.cuda.synchronize()
             assert torch.equal(got, want), (N, inner)
+
+
+@pytest.mark.parametrize("dtype,inners", [("f64", (15, 16, 17, 33, 64, 66, 127, 129, 131)),
+                                          ("f32", (31, 32, 33, 65, 129, 130, 255, 259))])
+def test_batch_windows_bitwise_plain(dtype, inners):
+    """A batch of plans whose rows take each form of the runs, with a plan with
+    b and one built without windows among them, in shapes whose workgroups
+    hold 1 to 4 items and loop over them."""
+    dt, tdt = (hb.F64, torch.float64) if dtype == "f64" else (hb.F32, torch.float32)
+    plans, inputs, want = [], [], []
+    for k, inner in enumerate(inners):
+        N, h = 9 + 4 * k, 1 + k % 3
+        _, prog = hb.cs_program(N, h, hb.CS_LAGRANGE)
+        if k == 2:
+            prog.add_vector([(0, 1), (0, N), (-h, 0)], np.linspace(-1, 1, N * h))
+        plans.append(hb.Plan(prog, inner=inner, dtype=dt, windows=k != 3))
+        inputs.append(torch.from_numpy(np.random.default_rng(k).normal(size=(prog.grid.cells, inner))).to(tdt).cuda())
+        want.append(inputs[-1].clone())
+        hb.apply(plans[-1], want[-1])
+    batch = hb.Batch(plans)
+    for tune in (None, dict(block=64, persistent=0), dict(block=192, persistent=0), dict(block=256, persistent=50)):
+        fields = [x.clone() for x in inputs]
+        batch.bind(fields)
+        if tune:
+            batch.tune = {**batch.tune, **tune}
+        batch.apply()
+        torch.cuda.synchronize()
+        assert all(torch.equal(f, w) for f, w in zip(fields, want)), tune
