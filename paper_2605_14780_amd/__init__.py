@@ -185,6 +185,10 @@ def _stream(stream):
     if stream is not None:
         return P(int(stream))
     import torch
+    # the current stream's handle, without the Stream object that
+    # torch.cuda.current_stream() makes (0.2 against 2.8 us of a 7 us call)
+    if torch.cuda.is_initialized():
+        return P(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     return P(int(torch.cuda.current_stream().cuda_stream))
 
 
