@@ -39,6 +39,9 @@ namespace hbc {
 // ---- per-launch descriptor of one plan applied to one field ---------------------------
 struct PlanDesc {
   void* field;
+  // several fields in one launch (k_apply_rows, k_apply_narrow): grid row y
+  // takes fields[y]; null: `field`
+  void* const* fields;
   const DevSeg* segs;
   const int32_t* ell_col;
   const void* ell_val;
@@ -73,6 +76,13 @@ struct AdjDesc {
   const int8_t* frot;
   int32_t aw;
 };
+
+// A pointer read from memory is generic to the compiler, and its accesses are
+// flat ones, which wait on the LDS counter too; this says that it is global.
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;  // (through an integer: else it folds away)
+}
 
 template <typename T, int V>
 struct Pack {
@@ -1110,6 +1120,7 @@ __global__ __launch_bounds__(256) void k_apply_narrow(PlanDesc d, const NarrowTi
                                                       int zero_only, const RowTile* __restrict__ ztiles,
                                                       int nnarrow) {
   constexpr int G = NARROW_LANES, IM = NARROW_ROW_BYTES / (int)sizeof(T);
+  if (d.fields) d.field = as_global(d.fields[blockIdx.y]);
   if ((int)blockIdx.x >= nnarrow) {  // a zero-row tile
     zero_row_tile<T>(d, ztiles[blockIdx.x - nnarrow]);
     return;
@@ -1231,6 +1242,7 @@ __device__ __forceinline__ void data_gather_rows(const PlanDesc& d, const DataDe
 template <typename T, int V, int U, bool NT, int RB, int KM>
 __global__ __launch_bounds__(256) void k_apply_rows(PlanDesc d, const RowTile* __restrict__ tiles, int ntiles,
                                                     int zero_only, DataDesc dd) {
+  if (d.fields) d.field = as_global(d.fields[blockIdx.y]);
   // the first dd.grid workgroups gather data rows (dispatched first, they
   // overlap the ghost-row tiles)
   if ((int)blockIdx.x < dd.grid) {
@@ -1438,7 +1450,16 @@ __global__ __launch_bounds__(256) void k_batch(const PlanDesc* __restrict__ desc
                                                int ntiles, const WinRun* __restrict__ runs) {
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const RowTile tl = tiles[t];
-    const PlanDesc d = descs[tl.pad_];
+    PlanDesc d = descs[tl.pad_];
+    d.field = as_global(d.field);
+    d.row_dst = as_global(d.row_dst);
+    d.row_src = as_global(d.row_src);
+    d.ell_col = as_global(d.ell_col);
+    d.ell_val = as_global(d.ell_val);
+    d.csr_ptr = as_global(d.csr_ptr);
+    d.csr_col = as_global(d.csr_col);
+    d.csr_val = as_global(d.csr_val);
+    d.bval = as_global(d.bval);
     if (tl.kind == SEG_RUNS) {
       if (d.ua)
         batch_runs<T, true>(d, tl, runs);
@@ -2829,13 +2850,13 @@ static thread_local std::vector<const void*>* t_rec = nullptr;
 
 template <typename T, int V, int U, int KX = 0>
 static void launch_rows_vu(const PlanDesc& d, hipStream_t st, int grid, int blk, const RowTile* tiles, int nt, int z,
-                           const DataDesc& dd) {
+                           const DataDesc& dd, int ny) {
   const bool rb2 = rows_per_batch(1 << d.lpr_shift) == 2;
   // FP64 rows take the row-by-row fallback of non-sliding Lagrange batches
   // (C768 x 32 with b: 9.5-9.9 against 10.6-10.8 us); FP32 rows keep the
   // batched one (measured: 7.1-7.4 against 6.5-6.6 us row by row)
   constexpr int KS = sizeof(T) == 8 ? KM_SEQFB : 0;
-  const dim3 g(grid + dd.grid), b(blk);
+  const dim3 g(grid + dd.grid, ny), b(blk);
   if (d.general) {
     if (d.nt && rb2)
       HBC_LAUNCH((k_apply_rows<T, V, U, true, 2, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
@@ -2860,28 +2881,28 @@ static void launch_rows_vu(const PlanDesc& d, hipStream_t st, int grid, int blk,
 // point-major row tiles: one instance per (vec, unroll) a plan can select
 template <typename T>
 static void launch_rows(const PlanDesc& d, hipStream_t st, int grid, int blk, const RowTile* tiles, int nt, int z,
-                        const DataDesc& dd) {
+                        const DataDesc& dd, int ny) {
   if (d.ua && dd.grid == 0) {
-    launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1, KM_UNAL>(d, st, grid, blk, tiles, nt, z, dd);
+    launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1, KM_UNAL>(d, st, grid, blk, tiles, nt, z, dd, ny);
     return;
   }
   if (sizeof(T) == 4) {
     if (d.vec == 4)
-      launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1>(d, st, grid, blk, tiles, nt, z, dd);
+      launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
     else if (d.vec == 2)
-      d.unroll >= 2 ? launch_rows_vu<T, 2, 2>(d, st, grid, blk, tiles, nt, z, dd)
-                    : launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd);
+      d.unroll >= 2 ? launch_rows_vu<T, 2, 2>(d, st, grid, blk, tiles, nt, z, dd, ny)
+                    : launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
     else if (d.unroll >= 4)
-      launch_rows_vu<T, 1, 4>(d, st, grid, blk, tiles, nt, z, dd);
+      launch_rows_vu<T, 1, 4>(d, st, grid, blk, tiles, nt, z, dd, ny);
     else
-      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd)
-                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd);
+      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd, ny)
+                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
   } else {
     if (d.vec >= 2)
-      launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd);
+      launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
     else
-      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd)
-                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd);
+      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd, ny)
+                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
   }
 }
 
@@ -3028,8 +3049,18 @@ static void launch_planes(const Plan& p, const PlanDesc& d, hipStream_t st, int 
   }
 }
 
+// Whether one apply is only the row and narrow kernels of a point-major plan
+// with too few workgroups to fill the chip (2 per CU): several fields then go
+// in one launch.  Larger applies gain only the launch's ramp, a few percent.
+static bool small_apply(const Plan& p) {
+  const HostTables& T = p.host;
+  if (p.layout.order != HBC_POINT_MAJOR || p.stats.rows_data > 0 || p.tune.persistent > 0) return false;
+  if (!T.wtiles.empty() || !T.wruns.empty() || !T.fruns.empty()) return false;
+  return T.rtiles.size() + T.ntiles.size() < 2 * 256;
+}
+
 template <typename T>
-static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only) {
+static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only, int ny = 1) {
   const bool pm = p.layout.order == HBC_POINT_MAJOR;
   const int nt = (int)(pm ? p.host.rtiles.size() : p.host.tiles.size());
   const int grid = p.tune.persistent > 0 ? std::min(p.tune.persistent, nt) : nt;
@@ -3051,7 +3082,7 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
     fold = p.host.rtiles[k].kind == SEG_ZERO && !p.host.rtiles[k].has_b;
   if (has_narrow) {
     const int nn = (int)p.host.ntiles.size();
-    HBC_LAUNCH((k_apply_narrow<T>), dim3(nn + (fold ? nt : 0)), dim3(256), 0, st, d, p.d_ntiles, z,
+    HBC_LAUNCH((k_apply_narrow<T>), dim3(nn + (fold ? nt : 0), ny), dim3(256), 0, st, d, p.d_ntiles, z,
                        p.d_rtiles, nn);
     HIP_CHECK(hipGetLastError());
   }
@@ -3080,7 +3111,7 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
     return;
   }
   if (fold || grid + dd.grid == 0) return;
-  launch_rows<T>(d, st, grid, blk, p.d_rtiles, nt, z, dd);
+  launch_rows<T>(d, st, grid, blk, p.d_rtiles, nt, z, dd, ny);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -3139,6 +3170,16 @@ void device_apply(const Plan& p, void* field, void* stream, bool zero_only) {
     launch_apply_t<float>(p, d, S(stream), zero_only);
     if (data_rows) launch_data_scatter_v<float>(p, d, S(stream));
   }
+}
+
+// One launch for the n fields of the device table `fields` (small_apply).
+static void device_apply_many(const Plan& p, void* const* fields, int n, void* stream) {
+  PlanDesc d = make_desc(p, nullptr);
+  d.fields = fields;
+  if (p.dtype == HBC_F64)
+    launch_apply_t<double>(p, d, S(stream), false, n);
+  else
+    launch_apply_t<float>(p, d, S(stream), false, n);
 }
 
 // The LDS adjoint's own launch shape, whatever the forward's tuning: 256
@@ -3571,7 +3612,24 @@ struct ApplyGraph {
   hipGraphExec_t exec = nullptr;
   const Plan* plan = nullptr;
   uint64_t gen = 0;  // the plan's tile generation at capture
+  void** d_fields = nullptr;  // fields that go several to a launch
 };
+
+// Applies that can share a launch: the longest run of the cycled fields from
+// rep r on whose memory is pairwise disjoint (an apply reads and writes its
+// own field only, so their order does not matter).
+static int disjoint_run(const Plan& p, void* const* fields, int nfields, int r, int reps) {
+  const size_t bytes = (size_t)p.grid.ncells * (size_t)p.layout.inner * (p.dtype == HBC_F64 ? 8 : 4);
+  int n = 1;
+  for (; r + n < reps && n < nfields; ++n) {
+    const char* f = static_cast<const char*>(fields[(r + n) % nfields]);
+    for (int k = 0; k < n; ++k) {
+      const char* g = static_cast<const char*>(fields[(r + k) % nfields]);
+      if (f < g + bytes && g < f + bytes) return n;
+    }
+  }
+  return n;
+}
 
 void* device_graph_create(const Plan& p, int op, void* const* fields, int nfields, int reps, void* stream) {
   if (!stream) fail(HBC_EINVAL, "graph capture needs a stream");
@@ -3579,13 +3637,27 @@ void* device_graph_create(const Plan& p, int op, void* const* fields, int nfield
   g->plan = &p;
   g->gen = p.tile_gen;
   hipStream_t s = S(stream);
-  hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+  const bool many = op == HBC_OP_APPLY && nfields > 1 && small_apply(p);
+  hipError_t e = hipSuccess;
+  if (many) {  // the cycled fields twice over: a run that wraps is contiguous
+    std::vector<void*> two(fields, fields + nfields);
+    two.insert(two.end(), fields, fields + nfields);
+    e = hipMalloc(reinterpret_cast<void**>(&g->d_fields), two.size() * sizeof(void*));
+    if (e == hipSuccess) e = hipMemcpy(g->d_fields, two.data(), two.size() * sizeof(void*), hipMemcpyHostToDevice);
+  }
+  if (e == hipSuccess) e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) {
-    delete g;
+    device_graph_destroy(g);
     fail(HBC_EHIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
   }
   try {
     for (int r = 0; r < reps; ++r) {
+      const int n = many ? std::min(disjoint_run(p, fields, nfields, r, reps), 1 << 15) : 1;
+      if (n > 1) {
+        device_apply_many(p, g->d_fields + r % nfields, n, stream);
+        r += n - 1;
+        continue;
+      }
       if (op == HBC_OP_ADJOINT)
         device_adjoint(p, fields[r % nfields], stream);
       else
@@ -3593,8 +3665,7 @@ void* device_graph_create(const Plan& p, int op, void* const* fields, int nfield
     }
   } catch (...) {
     (void)hipStreamEndCapture(s, &g->graph);
-    if (g->graph) (void)hipGraphDestroy(g->graph);
-    delete g;
+    device_graph_destroy(g);
     throw;
   }
   e = hipStreamEndCapture(s, &g->graph);
@@ -3619,6 +3690,7 @@ void device_graph_destroy(void* gp) {
   if (!g) return;
   if (g->exec) (void)hipGraphExecDestroy(g->exec);
   if (g->graph) (void)hipGraphDestroy(g->graph);
+  if (g->d_fields) (void)hipFree(g->d_fields);
   delete g;
 }
 

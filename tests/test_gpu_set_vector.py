@@ -94,3 +94,43 @@ def test_set_vector_reaches_a_batch_and_its_graph():
         batch.graph_launch(s.cuda_stream)
     torch.cuda.synchronize()
     assert torch.equal(fx, want)
+
+
+@pytest.mark.parametrize("inner,rows", [(1, "sync"), (3, "quad"), (5, "quad"), (2, "lagrange")])
+@pytest.mark.parametrize("nfields,reps", [(1, 3), (2, 1), (3, 3), (3, 8), (4, 11)])
+def test_graph_over_several_small_fields(inner, rows, nfields, reps):
+    """Small plans put the applies of a graph's cycled fields in shared
+    launches: as many as the repetitions reach, wrapping around the cycle, and
+    none of fields that overlap.  Every replay equals eager applies, with eager
+    work in between, and reads new b values."""
+    N, h = 10, 2
+    g = hb.Grid.cubed_sphere(N, h)
+    p = hb.Program(g)
+    if rows == "quad":
+        p.cs_add_quadrature(N, h, 2)
+    elif rows == "sync":
+        p.cs_add(N, h, hb.CS_SYNC)
+    else:
+        p = hb.cs_program(N, h, hb.CS_LAGRANGE)[1]
+    b = p.add_vector([(0, 1), (0, N), (-h, 0)], np.linspace(-1, 1, N * h))
+    plan = hb.Plan(p, inner=inner)
+    rng = np.random.default_rng(nfields)
+    pool = torch.from_numpy(rng.normal(size=nfields * plan.nelem)).cuda()
+    apart = [pool[k * plan.nelem:(k + 1) * plan.nelem] for k in range(nfields)]
+    shift = 2 * (plan.nelem // 4)  # a 16-byte boundary inside a field
+    lapped = [pool[k * shift:k * shift + plan.nelem] for k in range(nfields)]
+    s = torch.cuda.Stream()
+    for fields in (apart, lapped, [apart[0]] * nfields):
+        with torch.cuda.stream(s):
+            graph = hb.ApplyGraph(plan, fields, reps, stream=s.cuda_stream)
+            for rep in range(3):
+                start = torch.from_numpy(rng.normal(size=pool.numel())).cuda()
+                plan.set_vector(b, rng.normal(size=N * h))
+                pool.copy_(start)
+                for r in range(reps):
+                    hb.apply(plan, fields[r % nfields])
+                want = pool.clone()
+                pool.copy_(start)
+                graph.launch(s.cuda_stream)
+                s.synchronize()
+                assert torch.equal(pool, want), rep
