@@ -110,6 +110,15 @@ struct alignas(16) DataComp {
   int32_t col[DC_MAX];
 };
 
+// A component of at most DM_MAX columns and rows whose rows are all the same
+// combination of its columns (a mean of co-located points): one record, one
+// weight per column, one sum for all its rows.
+constexpr int DM_MAX = 4;
+struct alignas(16) DataMean {
+  int32_t col[DM_MAX], dst[DM_MAX];  // unused entries repeat the first
+  int32_t ncol, nrow, pad_[2];
+};
+
 // Rows on data cells (block-edge averaging): CSR over a box of one block's
 // data region, columns as global linear data indices.
 struct DataSub {
@@ -441,6 +450,8 @@ struct HostTables {
   std::vector<int32_t> dc_row_dst, dc_row_ent, dc_row_n;  // per component row
   std::vector<int32_t> dc_slot;                           // per entry: column slot in its component
   std::vector<double> dc_w;
+  std::vector<DataMean> dm;      // the components, where every one is a DataMean
+  std::vector<double> dm_w;      // DM_MAX weights per component
 };
 
 struct Layout {
@@ -517,6 +528,8 @@ struct Plan {
   const int32_t* d_dc_row_n = nullptr;
   const int32_t* d_dc_slot = nullptr;
   const void* d_dc_w = nullptr;
+  const DataMean* d_dm = nullptr;
+  const void* d_dm_w = nullptr;
   void* d_csc_dev = nullptr;  // allocation holding the adjoint tables
   const int64_t* d_csc_src = nullptr;
   const int64_t* d_csc_ptr = nullptr;

@@ -286,6 +286,32 @@ static void build_data_components(HostTables& T) {
     T.dc_comp.push_back(c);
   }
   T.dc_ok = true;
+  // components of equal rows
+  T.dm.clear();
+  T.dm_w.clear();
+  for (const DataComp& c : T.dc_comp) {
+    bool same = c.ncol >= 1 && c.ncol <= DM_MAX && c.nrow <= DM_MAX;
+    const int32_t first = same ? T.dc_row_ent[c.first_row] : 0;
+    for (int32_t k = 0; same && k < c.nrow; ++k) {
+      const int32_t e = T.dc_row_ent[c.first_row + k];
+      same = T.dc_row_n[c.first_row + k] == c.ncol;
+      for (int32_t m = 0; same && m < c.ncol; ++m) same = T.dc_slot[e + m] == m && T.dc_w[e + m] == T.dc_w[first + m];
+    }
+    if (!same) {
+      T.dm.clear();
+      T.dm_w.clear();
+      return;
+    }
+    DataMean d{};
+    d.ncol = c.ncol;
+    d.nrow = c.nrow;
+    for (int m = 0; m < DM_MAX; ++m) {
+      d.col[m] = c.col[m < c.ncol ? m : 0];
+      d.dst[m] = T.dc_row_dst[c.first_row + (m < c.nrow ? m : 0)];
+      T.dm_w.push_back(m < c.ncol ? T.dc_w[first + m] : 0.0);
+    }
+    T.dm.push_back(d);
+  }
 }
 
 // b values of one segment (Sec. III-B: the affine part of F, the sum of the

@@ -142,3 +142,39 @@ def test_custom_data_rows_chain(length):
     torch.cuda.synchronize()
     ref = oav.apply_with_data_rows(op, dop, u)
     assert np.array_equal(t.cpu().numpy(), ref, equal_nan=True)
+
+
+@pytest.mark.parametrize("inner,dtype", [(1, "f64"), (2, "f64"), (5, "f32"), (64, "f64"), (129, "f64"), (255, "f32"),
+                                         (256, "f64"), (260, "f64"), (516, "f32")])
+@pytest.mark.parametrize("sizes,equal", [((1,), True), ((2, 2, 3, 4), True), ((4, 5), True), ((2, 3), False)])
+def test_components_of_equal_and_other_rows(inner, dtype, sizes, equal):
+    """Sets of 1 to 4 points whose rows are one combination of the set, sets of
+    5, and sets whose rows differ: every row reads the input values."""
+    dt, tdt, eps = (hb.F64, torch.float64, 2.0 ** -53) if dtype == "f64" else (hb.F32, torch.float32, 2.0 ** -24)
+    rng = np.random.default_rng(len(sizes) + inner)
+    n = 40
+    g = hb.Grid([0], [n])
+    g.add_block([(0, n)], [(1, n - 1)])
+    p = hb.Program(g)
+    S = np.eye(n)
+    cells = 1 + rng.permutation(n - 2)[:sum(sizes)]
+    at = 0
+    for k in sizes:
+        members = np.sort(cells[at:at + k])
+        at += k
+        w = rng.uniform(0.1, 1.0, k).astype(np.float32).astype(np.float64)
+        for q, m in enumerate(members):
+            wq = w if equal else np.roll(w, q)
+            p.add_data_csr([(int(m), int(m) + 1)], [0, k], members, wq)
+            S[m] = 0
+            S[m, members] = wq
+    plan = hb.Plan(p, inner=inner, dtype=dt)
+    means = any("k_data_means" in k for k in plan.kernels())
+    assert means == (equal and max(sizes) <= 4)
+    x = rng.uniform(-1, 1, (n, inner)).astype(np.float32).astype(np.float64)
+    t = torch.from_numpy(x).to(tdt).cuda()
+    hb.apply(plan, t)
+    torch.cuda.synchronize()
+    # a row sums up to 5 products by FMAs: 5 roundings of at most sum |w x|
+    tol = 5 * eps * (np.abs(S) @ np.abs(x))
+    assert (np.abs(t.cpu().numpy().astype(np.float64) - S @ x) <= tol + 2.0 ** -52 * np.abs(x).max()).all()
