@@ -389,8 +389,10 @@ int hbc_time_apply(const hbc_plan* plan, void* const* fields, int64_t nelem, int
 /* Capture `reps` calls of `plan` (op HBC_OP_APPLY: hbc_apply; HBC_OP_ADJOINT:
  * hbc_apply_adjoint), cycling over the `nfields` device fields (each of
  * `nelem` values), into one HIP graph on `stream` (not NULL), for replay
- * without per-launch overhead.  The fields and the plan must stay alive while
- * the graph exists.  A later change of the plan's launch shape
+ * without per-launch overhead.  Applies of a small plan to disjoint fields
+ * share launches, and a graph of a few kernels is launched without a HIP graph
+ * where that is cheaper.  The fields and the plan must stay alive while the
+ * graph exists.  A later change of the plan's launch shape
  * (hbc_plan_set_tune, hbc_plan_autotune) makes hbc_graph_launch return
  * HBC_EINVAL without launching: capture the graph again. */
 #define HBC_OP_APPLY 0

@@ -3682,7 +3682,17 @@ struct ApplyGraph {
   const Plan* plan = nullptr;
   uint64_t gen = 0;  // the plan's tile generation at capture
   void** d_fields = nullptr;  // fields that go several to a launch
+  // A graph of at most GRAPH_DIRECT kernels is launched kernel by kernel: a
+  // graph launch costs the host about four kernel launches (C90 (h, u, v),
+  // one kernel: 16.5 us a replay through a graph, 6.5 us directly).
+  struct Call {
+    void* field;           // one field, or
+    void* const* fields;   // n of the device table
+    int n;
+  };
+  std::vector<Call> direct;
 };
+constexpr size_t GRAPH_DIRECT = 3;
 
 // Applies that can share a launch: the longest run of the cycled fields from
 // rep r on whose memory is pairwise disjoint (an apply reads and writes its
@@ -3700,6 +3710,13 @@ static int disjoint_run(const Plan& p, void* const* fields, int nfields, int r, 
   return n;
 }
 
+static void graph_call(const Plan& p, const ApplyGraph::Call& c, void* stream) {
+  if (c.n > 1)
+    device_apply_many(p, c.fields, c.n, stream);
+  else
+    device_apply(p, c.field, stream, false);
+}
+
 void* device_graph_create(const Plan& p, int op, void* const* fields, int nfields, int reps, void* stream) {
   if (!stream) fail(HBC_EINVAL, "graph capture needs a stream");
   auto* g = new ApplyGraph;
@@ -3713,24 +3730,38 @@ void* device_graph_create(const Plan& p, int op, void* const* fields, int nfield
     two.insert(two.end(), fields, fields + nfields);
     e = hipMalloc(reinterpret_cast<void**>(&g->d_fields), two.size() * sizeof(void*));
     if (e == hipSuccess) e = hipMemcpy(g->d_fields, two.data(), two.size() * sizeof(void*), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      device_graph_destroy(g);
+      fail(e == hipErrorOutOfMemory ? HBC_ENOMEM : HBC_EHIP, std::string("graph fields: ") + hipGetErrorString(e));
+    }
   }
-  if (e == hipSuccess) e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+  std::vector<ApplyGraph::Call> calls;
+  for (int r = 0; r < reps;) {
+    const int n = many ? std::min(disjoint_run(p, fields, nfields, r, reps), 1 << 15) : 1;
+    calls.push_back({fields[r % nfields], n > 1 ? g->d_fields + r % nfields : nullptr, n});
+    r += n;
+  }
+  try {
+    if (op == HBC_OP_APPLY && calls.size() <= GRAPH_DIRECT &&
+        calls.size() * device_kernel_names(p, HBC_OP_APPLY).size() <= GRAPH_DIRECT) {
+      g->direct = std::move(calls);
+      return g;
+    }
+  } catch (...) {
+    device_graph_destroy(g);
+    throw;
+  }
+  e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) {
     device_graph_destroy(g);
     fail(HBC_EHIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
   }
   try {
-    for (int r = 0; r < reps; ++r) {
-      const int n = many ? std::min(disjoint_run(p, fields, nfields, r, reps), 1 << 15) : 1;
-      if (n > 1) {
-        device_apply_many(p, g->d_fields + r % nfields, n, stream);
-        r += n - 1;
-        continue;
-      }
+    for (const ApplyGraph::Call& c : calls) {
       if (op == HBC_OP_ADJOINT)
-        device_adjoint(p, fields[r % nfields], stream);
+        device_adjoint(p, c.field, stream);
       else
-        device_apply(p, fields[r % nfields], stream, false);
+        graph_call(p, c, stream);
     }
   } catch (...) {
     (void)hipStreamEndCapture(s, &g->graph);
@@ -3751,6 +3782,10 @@ void device_graph_launch(void* gp, void* stream) {
   if (g->plan->tile_gen != g->gen)
     fail(HBC_EINVAL, "the plan's launch shape changed after this graph was captured (tuning rebuilds the tile "
                      "tables the graph points at); capture it again");
+  if (!g->direct.empty()) {
+    for (const ApplyGraph::Call& c : g->direct) graph_call(*g->plan, c, stream);
+    return;
+  }
   HIP_CHECK(hipGraphLaunch(g->exec, S(stream)));
 }
 
