@@ -1647,13 +1647,10 @@ void compute_stencil_info(Plan& p) {
         const int64_t src = T.row_src[sg.row_base + r];
         const int ob = (int)(std::upper_bound(firsts.begin(), firsts.end(), src) - firsts.begin()) - 1;
         const Block& O = g.blocks[ob];
-        int64_t off = src - O.first_cell;
-        bool match = true;
-        for (int d = 0; d < 4; ++d) {
-          const int64_t cd = O.full.lo[d] + off / O.stride[d];
-          off %= O.stride[d];
-          if (d > 0 && cd - O.data.lo[d] != pl[d - 1] - dd[d - 1] * n[d - 1]) match = false;
-        }
+        // the cell of O one block away (its box has one halo cell below the data)
+        int64_t want = O.first_cell;
+        for (int d = 0; d < 3; ++d) want += (pl[d] - dd[d] * n[d] + 1) * O.stride[d + 1];
+        const bool match = src == want;
         if (!match) {
           ok = false;
           no_fused("a halo copy is not a translation by one block");
