@@ -185,3 +185,34 @@ def test_batch_windows_bitwise_plain(dtype, inners):
         batch.apply()
         torch.cuda.synchronize()
         assert all(torch.equal(f, w) for f, w in zip(fields, want)), tune
+
+
+@pytest.mark.parametrize("rows,inner,dtype", [("lagrange", 33, "f64"), ("lagrange", 64, "f32"), ("quad", 3, "f64"),
+                                              ("quad", 40, "f64")])
+@pytest.mark.parametrize("ninner", [1, "inner"])
+def test_corner_rows_with_b_ride_in_the_strips_launch(rows, inner, dtype, ninner):
+    """b on zero rows (one corner of each face): the values are b, and the
+    adjoint zeroes the rows."""
+    dt, tdt = (hb.F64, torch.float64) if dtype == "f64" else (hb.F32, torch.float32)
+    N, h = 11, 2
+    n = inner if ninner == "inner" else 1
+    p = hb.Program(hb.Grid.cubed_sphere(N, h))
+    if rows == "quad":
+        p.cs_add_quadrature(N, h, 2)
+    else:
+        p = hb.cs_program(N, h, hb.CS_LAGRANGE)[1]
+    rng = np.random.default_rng(inner)
+    b = rng.normal(size=(6, h * h, n))
+    for f in range(6):
+        p.add_vector([(f, f + 1), (-h, 0), (N, N + h)], b[f], ninner=n)
+    plan = hb.Plan(p, inner=inner, dtype=dt)
+    x = torch.from_numpy(rng.normal(size=(p.grid.cells, inner))).to(tdt).cuda()
+    hb.apply(plan, x)
+    W = N + 2 * h
+    got = x.view(6, W, W, inner)[:, :h, N + h:].reshape(6, h * h, inner)
+    want = torch.from_numpy(b).to(tdt).cuda().expand(6, h * h, inner) if n == 1 else torch.from_numpy(b).to(tdt).cuda()
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    hb.apply_adjoint(plan, x)
+    torch.cuda.synchronize()
+    assert (x.view(6, W, W, inner)[:, :h] == 0).all()
