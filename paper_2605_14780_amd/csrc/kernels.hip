@@ -1914,10 +1914,17 @@ __global__ __launch_bounds__(256) void k_adjoint_wide(PlanDesc d, AdjWDesc q) {
   const int items = q.ntiles * q.nslices;
   int b = (int)blockIdx.x;
   if (b >= items) {
+    // (row, vector) pairs by two counters: their product passes 32 bits on rows of 2^25 vectors
     const int nvec = inner / V, r0 = (b - items) * ADJ_ZERO_ROWS, nr = min(ADJ_ZERO_ROWS, q.nzero - r0);
-    for (int e = tid; e < nr * nvec; e += 256) {
-      const int r = e / nvec, v = e - r * nvec;
+    const int dr = 256 / nvec, dv = 256 - dr * nvec;
+    for (int r = tid / nvec, v = tid - r * nvec; r < nr;) {
       stv<T, V, NT>(f + (int64_t)q.zero[r0 + r] * d.cs + (int64_t)v * V, zero);
+      r += dr;
+      v += dv;
+      if (v >= nvec) {
+        v -= nvec;
+        ++r;
+      }
     }
     return;
   }
