@@ -494,6 +494,7 @@ class ApplyGraph:
         arr = (P * len(ptrs))(*[p for p, _ in ptrs])
         self._h = P()
         self._fields = list(fields)  # keep the memory alive with the graph
+        self.plan = plan  # the library keeps a pointer to the plan
         self.reps = reps
         _check(lib().hbc_graph_create(plan._h, op, arr, ptrs[0][1], len(ptrs), reps, _stream(stream),
                                       C.byref(self._h)))
