@@ -3,6 +3,9 @@ import gc
 import types
 import weakref
 
+import pytest
+import torch
+
 import paper_2605_14780_amd as hb
 
 
@@ -24,3 +27,13 @@ def test_graph_keeps_its_plan_and_fields(monkeypatch):
     del graph
     gc.collect()
     assert all(r() is None for r in alive)
+
+
+@pytest.mark.parametrize("name", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torch_private_names(monkeypatch, name):
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=48))
+    for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.setattr(torch._C, n, lambda *a: 0, raising=False)
+    monkeypatch.delattr(torch._C, name)
+    assert hb._stream(None).value == 48
