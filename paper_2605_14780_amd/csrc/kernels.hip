@@ -1350,13 +1350,13 @@ __global__ __launch_bounds__(256) void k_apply_planes(PlanDesc d, PlaneRows t, i
         for (int i = tid; i < pc.nu; i += nthr) {
           const int64_t cell = t.ucell[pc.first_u + i];
           const int rot = ROT ? t.urot[pc.first_u + i] : 0;
-          T x[PB], sign[PB];
+          T x[PB], sign;
 #pragma unroll
           for (int u = 0; u < PB; ++u)
-            if (u < np) x[u] = source(p0 + u, rot, sign[u])[cell];
+            if (u < np) x[u] = source(p0 + u, rot, sign)[cell];
 #pragma unroll
           for (int u = 0; u < PB; ++u)
-            if (u < np) lds[u * t.ustride + i] = sign[u] * x[u];
+            if (u < np) lds[u * t.ustride + i] = x[u];
         }
     }
     for (int r = tid; r - tid < pc.nrows; r += nthr) {
@@ -1364,9 +1364,10 @@ __global__ __launch_bounds__(256) void k_apply_planes(PlanDesc d, PlaneRows t, i
       const int64_t row = pc.row0 + (live ? r : 0);
       const int64_t dst = t.dst[row];
       const int meta = t.meta[row];
-      const int ne = zero_only ? 0 : meta & 15;
+      const int ne = zero_only ? 0 : meta & 15, rot = zero_only ? 0 : meta >> PM_ROT_SHIFT;
       const Pack<T, ME> w = ldv<T, ME>(static_cast<const T*>(t.w) + row * ME);
-      T y[PB];
+      // the sign goes on the sum, as in every other kernel (it shows where a sum cancels to zero)
+      T y[PB], sign[PB];
       if constexpr (ME > 1) {
         const Pack<uint16_t, ME> c = ldv<uint16_t, ME>(t.slot + row * ME);
         if (r == tid) __syncthreads();
@@ -1378,19 +1379,21 @@ __global__ __launch_bounds__(256) void k_apply_planes(PlanDesc d, PlaneRows t, i
 #pragma unroll
             for (int m = 0; m < ME; ++m)
               if (m < ne) y[u] = m == 0 ? w.v[0] * xl[c.v[0]] : fma(w.v[m], xl[c.v[m]], y[u]);
+            source(p0 + u, rot, sign[u]);
+            y[u] = sign[u] * y[u];
           }
         }
       } else {
         const int64_t col = t.col[row];
-        const int rot = meta >> PM_ROT_SHIFT;
-        T x[PB], sign[PB];
-        if (ne > 0) {
+        T x[PB];
 #pragma unroll
-          for (int u = 0; u < PB; ++u)
-            if (u < np) x[u] = source(p0 + u, rot, sign[u])[col];
-        }
+        for (int u = 0; u < PB; ++u)
+          if (u < np) {
+            const T* from = source(p0 + u, rot, sign[u]);
+            x[u] = ne > 0 ? from[col] : T(0);
+          }
 #pragma unroll
-        for (int u = 0; u < PB; ++u) y[u] = ne > 0 && u < np ? sign[u] * (w.v[0] * x[u]) : T(0);
+        for (int u = 0; u < PB; ++u) y[u] = u < np ? sign[u] * (ne > 0 ? w.v[0] * x[u] : T(0)) : T(0);
       }
       if (!zero_only && (meta & PM_HAS_B)) {
         const T* bp = static_cast<const T*>(d.bval) + t.brow[row];

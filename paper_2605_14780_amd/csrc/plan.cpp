@@ -1134,7 +1134,8 @@ static void build_planes(Plan& plan) {
         T.p_slot[at + m] = (uint16_t)bucket[f];
       }
       T.p_dst.push_back(T.row_dst[row]);
-      T.p_meta.push_back(ne | (ne > 0 ? sg.rot << PM_ROT_SHIFT : 0));
+      const bool sum = sg.kind == SEG_MAP || sg.kind == SEG_ELL || sg.kind == SEG_CSR;  // (an empty one too)
+      T.p_meta.push_back(ne | (sum ? sg.rot << PM_ROT_SHIFT : 0));
       T.p_brow.push_back(0);
       if (sg.has_b) {
         T.p_meta.back() |= PM_HAS_B | (sg.b_inner > 1 ? PM_B_INNER : 0) | (sg.kind == SEG_VEC ? PM_B_ONLY : 0);

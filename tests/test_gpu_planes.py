@@ -43,3 +43,41 @@ def test_plane_major_matches_point_major(N, h, I, vec, dtype, mode, ninner):
         hb.apply(plan, got)
         torch.cuda.synchronize()
         assert torch.equal(got.t(), want)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("width", [1, 2])
+def test_plane_major_zeros_have_the_sign_of_point_major(dtype, width):
+    """Rows whose sums cancel, copies of +0 and rows without entries, under
+    every component rotation: the sign applies to the sum, so a negated
+    component is -0, in both layouts."""
+    dt, tdt = (hb.F64, torch.float64) if dtype == "f64" else (hb.F32, torch.float32)
+    rots = [(s, 0, 0, t) for s in (1, -1) for t in (1, -1)] + [(0, s, t, 0) for s in (1, -1) for t in (1, -1)]
+    n, I, vec = 8 * 3 + 2, 6, (2, 2, 2)
+    g = hb.Grid([0], [n])
+    g.add_block([(0, n)], [(24, 26)])
+    p = hb.Program(g)
+    neg = torch.zeros(n, I, dtype=torch.bool)
+    for k, r in enumerate(rots):
+        if width == 1:
+            p.add_ell([(k, k + 1)], 1, [24], [2.0], rot=r)
+        else:
+            p.add_ell([(k, k + 1)], 2, [24, 25], [1.0, -1.0], rot=r)
+        p.add_map([(8 + k, 9 + k)], [[0]], [24], rot=r)
+        p.add_csr([(16 + k, 17 + k)], [0, 0], [], [], rot=r)
+        for a, s in enumerate((r[0] + r[1], r[2] + r[3])):
+            for row in (k, 8 + k, 16 + k):
+                neg[row, 2 + 2 * a:4 + 2 * a] = s < 0
+    x = torch.full((n, I), 3.0)
+    x[24:] = 0.0 if width == 1 else 1.0  # copies of 1 need no sign of zero: only the sums cancel
+    zero = torch.zeros(n, dtype=torch.bool)
+    zero[:24] = True
+    if width == 2:
+        zero[8:16] = False
+    point, plane = x.to(tdt).cuda(), x.t().contiguous().to(tdt).cuda()
+    hb.apply(hb.Plan(p, inner=I, vec=vec, dtype=dt), point)
+    hb.apply(hb.Plan(p, inner=I, vec=vec, dtype=dt, order=hb.PLANE_MAJOR), plane)
+    torch.cuda.synchronize()
+    for got in (point.cpu(), plane.t().cpu()):
+        assert (got[zero] == 0).all()
+        assert torch.equal(torch.signbit(got[zero]), neg[zero])
