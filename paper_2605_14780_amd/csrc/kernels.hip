@@ -39,9 +39,6 @@ namespace hbc {
 // ---- per-launch descriptor of one plan applied to one field ---------------------------
 struct PlanDesc {
   void* field;
-  // several fields in one launch (k_apply_rows, k_apply_narrow): grid row y
-  // takes fields[y]; null: `field`
-  void* const* fields;
   const DevSeg* segs;
   const int32_t* ell_col;
   const void* ell_val;
@@ -82,6 +79,22 @@ struct AdjDesc {
 template <typename T>
 __device__ __forceinline__ T* as_global(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;  // (through an integer: else it folds away)
+}
+
+// Several fields in one launch (k_apply_rows, k_apply_narrow): grid row y takes
+// p[y] instead of the descriptor's field.  They travel in the kernel's
+// arguments: a table in device memory would have to be allocated, copied and
+// freed beside captures that the caller may have open.
+constexpr int FIELDS_PER_LAUNCH = 8;
+struct FieldSet {
+  int32_t n = 1;
+  void* p[FIELDS_PER_LAUNCH] = {};
+};
+__device__ __forceinline__ void* field_of(const FieldSet& fs, int y) {
+  void* f = fs.p[0];
+#pragma unroll
+  for (int k = 1; k < FIELDS_PER_LAUNCH; ++k) f = y == k ? fs.p[k] : f;
+  return as_global(f);
 }
 
 template <typename T, int V>
@@ -1127,9 +1140,9 @@ __global__ __launch_bounds__(256) void k_apply_wide(PlanDesc d, const WideTile* 
 template <typename T>
 __global__ __launch_bounds__(256) void k_apply_narrow(PlanDesc d, const NarrowTile* __restrict__ tiles,
                                                       int zero_only, const RowTile* __restrict__ ztiles,
-                                                      int nnarrow) {
+                                                      int nnarrow, FieldSet fs) {
   constexpr int G = NARROW_LANES, IM = NARROW_ROW_BYTES / (int)sizeof(T);
-  if (d.fields) d.field = as_global(d.fields[blockIdx.y]);
+  if (fs.n > 1) d.field = field_of(fs, (int)blockIdx.y);
   if ((int)blockIdx.x >= nnarrow) {  // a zero-row tile
     zero_row_tile<T, true>(d, ztiles[blockIdx.x - nnarrow], zero_only);
     return;
@@ -1250,8 +1263,8 @@ __device__ __forceinline__ void data_gather_rows(const PlanDesc& d, const DataDe
 
 template <typename T, int V, int U, bool NT, int RB, int KM>
 __global__ __launch_bounds__(256) void k_apply_rows(PlanDesc d, const RowTile* __restrict__ tiles, int ntiles,
-                                                    int zero_only, DataDesc dd) {
-  if (d.fields) d.field = as_global(d.fields[blockIdx.y]);
+                                                    int zero_only, DataDesc dd, FieldSet fs) {
+  if (fs.n > 1) d.field = field_of(fs, (int)blockIdx.y);
   // the first dd.grid workgroups gather data rows (dispatched first, they
   // overlap the ghost-row tiles)
   if ((int)blockIdx.x < dd.grid) {
@@ -2918,59 +2931,59 @@ static thread_local std::vector<const void*>* t_rec = nullptr;
 
 template <typename T, int V, int U, int KX = 0>
 static void launch_rows_vu(const PlanDesc& d, hipStream_t st, int grid, int blk, const RowTile* tiles, int nt, int z,
-                           const DataDesc& dd, int ny) {
+                           const DataDesc& dd, const FieldSet& fs) {
   const bool rb2 = rows_per_batch(1 << d.lpr_shift) == 2;
   // FP64 rows take the row-by-row fallback of non-sliding Lagrange batches
   // (C768 x 32 with b: 9.5-9.9 against 10.6-10.8 us); FP32 rows keep the
   // batched one (measured: 7.1-7.4 against 6.5-6.6 us row by row)
   constexpr int KS = sizeof(T) == 8 ? KM_SEQFB : 0;
-  const dim3 g(grid + dd.grid, ny), b(blk);
+  const dim3 g(grid + dd.grid, fs.n), b(blk);
   if (d.general) {
     if (d.nt && rb2)
-      HBC_LAUNCH((k_apply_rows<T, V, U, true, 2, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, true, 2, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
     else if (d.nt)
-      HBC_LAUNCH((k_apply_rows<T, V, U, true, 4, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, true, 4, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
     else if (rb2)
-      HBC_LAUNCH((k_apply_rows<T, V, U, false, 2, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, false, 2, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
     else
-      HBC_LAUNCH((k_apply_rows<T, V, U, false, 4, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, false, 4, 3 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
   } else {
     if (d.nt && rb2)
-      HBC_LAUNCH((k_apply_rows<T, V, U, true, 2, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, true, 2, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
     else if (d.nt)
-      HBC_LAUNCH((k_apply_rows<T, V, U, true, 4, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, true, 4, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
     else if (rb2)
-      HBC_LAUNCH((k_apply_rows<T, V, U, false, 2, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, false, 2, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
     else
-      HBC_LAUNCH((k_apply_rows<T, V, U, false, 4, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd);
+      HBC_LAUNCH((k_apply_rows<T, V, U, false, 4, 1 | KX | KS>), g, b, 0, st, d, tiles, nt, z, dd, fs);
   }
 }
 
 // point-major row tiles: one instance per (vec, unroll) a plan can select
 template <typename T>
 static void launch_rows(const PlanDesc& d, hipStream_t st, int grid, int blk, const RowTile* tiles, int nt, int z,
-                        const DataDesc& dd, int ny) {
+                        const DataDesc& dd, const FieldSet& fs) {
   if (d.ua && dd.grid == 0) {
-    launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1, KM_UNAL>(d, st, grid, blk, tiles, nt, z, dd, ny);
+    launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1, KM_UNAL>(d, st, grid, blk, tiles, nt, z, dd, fs);
     return;
   }
   if (sizeof(T) == 4) {
     if (d.vec == 4)
-      launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
+      launch_rows_vu<T, (sizeof(T) == 4 ? 4 : 2), 1>(d, st, grid, blk, tiles, nt, z, dd, fs);
     else if (d.vec == 2)
-      d.unroll >= 2 ? launch_rows_vu<T, 2, 2>(d, st, grid, blk, tiles, nt, z, dd, ny)
-                    : launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
+      d.unroll >= 2 ? launch_rows_vu<T, 2, 2>(d, st, grid, blk, tiles, nt, z, dd, fs)
+                    : launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd, fs);
     else if (d.unroll >= 4)
-      launch_rows_vu<T, 1, 4>(d, st, grid, blk, tiles, nt, z, dd, ny);
+      launch_rows_vu<T, 1, 4>(d, st, grid, blk, tiles, nt, z, dd, fs);
     else
-      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd, ny)
-                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
+      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd, fs)
+                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd, fs);
   } else {
     if (d.vec >= 2)
-      launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
+      launch_rows_vu<T, 2, 1>(d, st, grid, blk, tiles, nt, z, dd, fs);
     else
-      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd, ny)
-                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd, ny);
+      d.unroll >= 2 ? launch_rows_vu<T, 1, 2>(d, st, grid, blk, tiles, nt, z, dd, fs)
+                    : launch_rows_vu<T, 1, 1>(d, st, grid, blk, tiles, nt, z, dd, fs);
   }
 }
 
@@ -3128,7 +3141,8 @@ static bool small_apply(const Plan& p) {
 }
 
 template <typename T>
-static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only, int ny = 1) {
+static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only,
+                           const FieldSet& fs = FieldSet{}) {
   const bool pm = p.layout.order == HBC_POINT_MAJOR;
   const int nt = (int)(pm ? p.host.rtiles.size() : p.host.tiles.size());
   const int grid = p.tune.persistent > 0 ? std::min(p.tune.persistent, nt) : nt;
@@ -3151,8 +3165,8 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
            (has_narrow || !has_wide || !p.host.rtiles[k].has_b);
   if (has_narrow) {
     const int nn = (int)p.host.ntiles.size();
-    HBC_LAUNCH((k_apply_narrow<T>), dim3(nn + (fold ? nt : 0), ny), dim3(256), 0, st, d, p.d_ntiles, z,
-                       p.d_rtiles, nn);
+    HBC_LAUNCH((k_apply_narrow<T>), dim3(nn + (fold ? nt : 0), fs.n), dim3(256), 0, st, d, p.d_ntiles, z,
+                       p.d_rtiles, nn, fs);
     HIP_CHECK(hipGetLastError());
   }
   if (has_wide) {
@@ -3180,7 +3194,7 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
     return;
   }
   if (fold || grid + dd.grid == 0) return;
-  launch_rows<T>(d, st, grid, blk, p.d_rtiles, nt, z, dd, ny);
+  launch_rows<T>(d, st, grid, blk, p.d_rtiles, nt, z, dd, fs);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -3261,14 +3275,13 @@ void device_apply(const Plan& p, void* field, void* stream, bool zero_only) {
   }
 }
 
-// One launch for the n fields of the device table `fields` (small_apply).
-static void device_apply_many(const Plan& p, void* const* fields, int n, void* stream) {
-  PlanDesc d = make_desc(p, nullptr);
-  d.fields = fields;
+// One launch for the fields of fs (small_apply).
+static void device_apply_many(const Plan& p, const FieldSet& fs, void* stream) {
+  const PlanDesc d = make_desc(p, fs.p[0]);
   if (p.dtype == HBC_F64)
-    launch_apply_t<double>(p, d, S(stream), false, n);
+    launch_apply_t<double>(p, d, S(stream), false, fs);
   else
-    launch_apply_t<float>(p, d, S(stream), false, n);
+    launch_apply_t<float>(p, d, S(stream), false, fs);
 }
 
 // The LDS adjoint's own launch shape, whatever the forward's tuning: 256
@@ -3701,66 +3714,48 @@ struct ApplyGraph {
   hipGraphExec_t exec = nullptr;
   const Plan* plan = nullptr;
   uint64_t gen = 0;  // the plan's tile generation at capture
-  void** d_fields = nullptr;  // fields that go several to a launch
   // A graph of at most GRAPH_DIRECT kernels is launched kernel by kernel: a
   // graph launch costs the host about four kernel launches (C90 (h, u, v),
   // one kernel: 16.5 us a replay through a graph, 6.5 us directly).
-  struct Call {
-    void* field;           // one field, or
-    void* const* fields;   // n of the device table
-    int n;
-  };
-  std::vector<Call> direct;
+  std::vector<FieldSet> direct;  // the fields of each launch
 };
 constexpr size_t GRAPH_DIRECT = 3;
 
 // Applies that can share a launch: the longest run of the cycled fields from
 // rep r on whose memory is pairwise disjoint (an apply reads and writes its
 // own field only, so their order does not matter).
-static int disjoint_run(const Plan& p, void* const* fields, int nfields, int r, int reps) {
+static FieldSet disjoint_run(const Plan& p, void* const* fields, int nfields, int r, int reps) {
   const size_t bytes = (size_t)p.grid.ncells * (size_t)p.layout.inner * (p.dtype == HBC_F64 ? 8 : 4);
-  int n = 1;
-  for (; r + n < reps && n < nfields; ++n) {
-    const char* f = static_cast<const char*>(fields[(r + n) % nfields]);
-    for (int k = 0; k < n; ++k) {
-      const char* g = static_cast<const char*>(fields[(r + k) % nfields]);
-      if (f < g + bytes && g < f + bytes) return n;
+  FieldSet fs;
+  fs.p[0] = fields[r % nfields];
+  for (; r + fs.n < reps && fs.n < FIELDS_PER_LAUNCH; ++fs.n) {
+    char* f = static_cast<char*>(fields[(r + fs.n) % nfields]);
+    for (int k = 0; k < fs.n; ++k) {
+      const char* g = static_cast<const char*>(fs.p[k]);
+      if (f < g + bytes && g < f + bytes) return fs;
     }
+    fs.p[fs.n] = f;
   }
-  return n;
+  return fs;
 }
 
-static void graph_call(const Plan& p, const ApplyGraph::Call& c, void* stream) {
-  if (c.n > 1)
-    device_apply_many(p, c.fields, c.n, stream);
+static void graph_call(const Plan& p, const FieldSet& fs, void* stream) {
+  if (fs.n > 1)
+    device_apply_many(p, fs, stream);
   else
-    device_apply(p, c.field, stream, false);
+    device_apply(p, fs.p[0], stream, false);
 }
 
 void* device_graph_create(const Plan& p, int op, void* const* fields, int nfields, int reps, void* stream) {
   if (!stream) fail(HBC_EINVAL, "graph capture needs a stream");
+  const bool many = op == HBC_OP_APPLY && nfields > 1 && small_apply(p);
+  std::vector<FieldSet> calls;
+  for (int r = 0; r < reps; r += calls.back().n)
+    calls.push_back(disjoint_run(p, fields, nfields, r, many ? reps : r + 1));
   auto* g = new ApplyGraph;
   g->plan = &p;
   g->gen = p.tile_gen;
   hipStream_t s = S(stream);
-  const bool many = op == HBC_OP_APPLY && nfields > 1 && small_apply(p);
-  hipError_t e = hipSuccess;
-  if (many) {  // the cycled fields twice over: a run that wraps is contiguous
-    std::vector<void*> two(fields, fields + nfields);
-    two.insert(two.end(), fields, fields + nfields);
-    e = hipMalloc(reinterpret_cast<void**>(&g->d_fields), two.size() * sizeof(void*));
-    if (e == hipSuccess) e = hipMemcpy(g->d_fields, two.data(), two.size() * sizeof(void*), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      device_graph_destroy(g);
-      fail(e == hipErrorOutOfMemory ? HBC_ENOMEM : HBC_EHIP, std::string("graph fields: ") + hipGetErrorString(e));
-    }
-  }
-  std::vector<ApplyGraph::Call> calls;
-  for (int r = 0; r < reps;) {
-    const int n = many ? std::min(disjoint_run(p, fields, nfields, r, reps), 1 << 15) : 1;
-    calls.push_back({fields[r % nfields], n > 1 ? g->d_fields + r % nfields : nullptr, n});
-    r += n;
-  }
   try {
     if (op == HBC_OP_APPLY && calls.size() <= GRAPH_DIRECT &&
         calls.size() * device_kernel_names(p, HBC_OP_APPLY).size() <= GRAPH_DIRECT) {
@@ -3771,15 +3766,15 @@ void* device_graph_create(const Plan& p, int op, void* const* fields, int nfield
     device_graph_destroy(g);
     throw;
   }
-  e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+  hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) {
     device_graph_destroy(g);
     fail(HBC_EHIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
   }
   try {
-    for (const ApplyGraph::Call& c : calls) {
+    for (const FieldSet& c : calls) {
       if (op == HBC_OP_ADJOINT)
-        device_adjoint(p, c.field, stream);
+        device_adjoint(p, c.p[0], stream);
       else
         graph_call(p, c, stream);
     }
@@ -3803,7 +3798,7 @@ void device_graph_launch(void* gp, void* stream) {
     fail(HBC_EINVAL, "the plan's launch shape changed after this graph was captured (tuning rebuilds the tile "
                      "tables the graph points at); capture it again");
   if (!g->direct.empty()) {
-    for (const ApplyGraph::Call& c : g->direct) graph_call(*g->plan, c, stream);
+    for (const FieldSet& c : g->direct) graph_call(*g->plan, c, stream);
     return;
   }
   HIP_CHECK(hipGraphLaunch(g->exec, S(stream)));
@@ -3814,7 +3809,6 @@ void device_graph_destroy(void* gp) {
   if (!g) return;
   if (g->exec) (void)hipGraphExecDestroy(g->exec);
   if (g->graph) (void)hipGraphDestroy(g->graph);
-  if (g->d_fields) (void)hipFree(g->d_fields);
   delete g;
 }
 
