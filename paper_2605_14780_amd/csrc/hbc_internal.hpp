@@ -405,6 +405,10 @@ struct HostTables {
   std::vector<int32_t> row_dst;  // destination cell of every covered row
   std::vector<int32_t> row_src;  // MAP rows: source cell; other rows: 0
   std::vector<RowTile> rtiles;
+  // what a launch asks of all rtiles, kept with them (a scan of 27000 tiles in
+  // every call cost the host 12 us): general ELL/CSR rows among them; none but
+  // zero and b-only rows; any of those with b
+  bool rt_general = false, rt_light = false, rt_light_b = false;
   // wide rows (see WideTile); seg_wide marks the segments they take
   std::vector<char> seg_wide;
   std::vector<WideTile> wtiles;

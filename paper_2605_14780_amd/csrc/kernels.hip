@@ -2676,9 +2676,7 @@ PlanDesc make_desc(const Plan& p, void* field) {
   d.chunked = p.tune.lanes_per_row >= CHUNK_LPR ? 1 : 0;
   d.nt = (p.layout.order == HBC_POINT_MAJOR && p.layout.inner * (p.dtype == HBC_F64 ? 8 : 4) >= 128) ? 1 : 0;
   d.unroll = p.unroll;
-  d.general = 0;
-  for (const RowTile& t : p.host.rtiles)
-    if (t.kind == SEG_CSR || (t.kind == SEG_ELL && (t.width != 4 || (t.flags & SEGF_ELL_PADDED)))) d.general = 1;
+  d.general = p.host.rt_general;
   d.ua = unaligned_rows(p);
   return d;
 }
@@ -3159,10 +3157,8 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
   // all zero or b-only rows (the corners of the cubed-sphere programs)
   const bool has_narrow = pm && !p.host.ntiles.empty(), has_wide = pm && !p.host.wtiles.empty();
   const bool has_win = pm && !p.host.wruns.empty(), has_fixed = pm && !p.host.fruns.empty();
-  bool fold = (has_narrow || has_wide || has_win || has_fixed) && dd.grid == 0 && nt > 0;
-  for (size_t k = 0; fold && k < p.host.rtiles.size(); ++k)
-    fold = (p.host.rtiles[k].kind == SEG_ZERO || p.host.rtiles[k].kind == SEG_VEC) &&
-           (has_narrow || !has_wide || !p.host.rtiles[k].has_b);
+  const bool fold = (has_narrow || has_wide || has_win || has_fixed) && dd.grid == 0 && nt > 0 && p.host.rt_light &&
+                    (has_narrow || !has_wide || !p.host.rt_light_b);
   if (has_narrow) {
     const int nn = (int)p.host.ntiles.size();
     HBC_LAUNCH((k_apply_narrow<T>), dim3(nn + (fold ? nt : 0), fs.n), dim3(256), 0, st, d, p.d_ntiles, z,
@@ -3715,8 +3711,10 @@ struct ApplyGraph {
   const Plan* plan = nullptr;
   uint64_t gen = 0;  // the plan's tile generation at capture
   // A graph of at most GRAPH_DIRECT kernels is launched kernel by kernel: a
-  // graph launch costs the host about four kernel launches (C90 (h, u, v),
-  // one kernel: 16.5 us a replay through a graph, 6.5 us directly).
+  // replay through a HIP graph costs the host 16-18 us whatever it holds; 1,
+  // 2 and 3 kernels launched directly 3.2, 5.6 and 8.3 us (C24 to C384
+  // copies and strips, 50 to 27000 tiles; C90 (h, u, v) quadrature rows, one
+  // kernel: 16.5 us a replay through a graph, 6.5 us directly).
   std::vector<FieldSet> direct;  // the fields of each launch
 };
 constexpr size_t GRAPH_DIRECT = 3;

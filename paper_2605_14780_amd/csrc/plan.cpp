@@ -1312,6 +1312,14 @@ void build_tiles(Plan& plan, const hbc_tune& t) {
     rt.b_inner = sg.b_inner;
     plan.host.rtiles.push_back(rt);
   }
+  HostTables& T = plan.host;
+  T.rt_general = T.rt_light_b = false;
+  T.rt_light = true;
+  for (const RowTile& t : T.rtiles) {
+    if (t.kind == SEG_CSR || (t.kind == SEG_ELL && (t.width != 4 || (t.flags & SEGF_ELL_PADDED)))) T.rt_general = true;
+    T.rt_light = T.rt_light && (t.kind == SEG_ZERO || t.kind == SEG_VEC);
+    T.rt_light_b = T.rt_light_b || t.has_b;
+  }
 }
 
 // Tiles of the LDS-staged adjoint: consecutive sources, greedily, while the

@@ -1,4 +1,6 @@
 """Graphs of applies beside what else a program captures."""
+import time
+
 import pytest
 
 from helpers import gpu_available
@@ -42,3 +44,30 @@ def test_graph_made_and_dropped_while_another_stream_captures(nfields, reps):
         torch.cuda.synchronize()
         assert (y == 2).all(), rep
         assert all(torch.equal(x, w) for x, w in zip(xs, want)), rep
+
+
+@pytest.mark.parametrize("call", ["apply", "graph"])
+def test_host_time_of_a_call_does_not_grow_with_the_tiles(call):
+    """A call reads nothing per tile on the host: 27000 tiles cost it what 50
+    do (a scan of them takes 12 us, a launch 3)."""
+    host = {}
+    for N, rows in ((384, 1), (8, 512)):
+        p = hb.Program(hb.Grid.cubed_sphere(N, 3))
+        p.cs_add(N, 3, hb.CS_SYNC)
+        plan = hb.Plan(p, inner=1)
+        plan.tune = {**plan.tune, "block": 64, "lanes_per_row": 1, "rows_per_tile": rows}
+        x = torch.zeros(plan.nelem, device="cuda", dtype=torch.float64)
+        s = torch.cuda.Stream()
+        graph = hb.ApplyGraph(plan, [x], 1, stream=s.cuda_stream)
+        once = (lambda: graph.launch(s.cuda_stream)) if call == "graph" else (lambda: hb.apply(plan, x, s.cuda_stream))
+        times = []
+        for _ in range(30):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(20):
+                once()
+            times.append((time.perf_counter() - t) / 20)
+        host[plan.stats()["tiles"]] = min(times)
+    (few, least), (many, most) = sorted(host.items())
+    assert few < 60 and many > 27000
+    assert most <= least + 8e-6
