@@ -554,24 +554,46 @@ __device__ __forceinline__ void rt_tile(const PlanDesc& d, const RowTile& tl, bo
 }
 
 // Zero rows and b-only rows of a row tile (point-major), written by extra
-// workgroups of the wide-row, narrow and window launches when those are all a
-// plan's other rows, so that such a plan needs one launch (C768 x 32 FP64 with
-// b on every ghost: 9.8 -> 7.8 us).  B: the tiles may carry b; the wide kernel
+// workgroups (256 threads) of the wide-row, narrow and window launches when
+// those are all a plan's other rows, so that such a plan needs one launch
+// (C768 x 32 FP64 with b on every ghost: 9.8 -> 7.8 us).  Vectors as in the
+// launch's own rows, (row, vector) pairs by two counters, so that plans of
+// mostly such rows gain too: C384 x 137 FP32 with one strip of window rows and
+// b on every other side 10.4 us with one value per lane and a division each,
+// 7.0 in a launch of the row kernel, 6.5 so (x 32: 7.0, 3.6 and 3.9; C24 x 257
+// 3.5 in the row kernel, 3.7 so).  B: the tiles may carry b; the wide kernel
 // keeps the form without (C384 x 256 45.0 us, 45.4 with b compiled in).
-template <typename T, bool B>
+template <typename T, int V, bool NT, bool UA, bool B>
 __device__ __forceinline__ void zero_row_tile(const PlanDesc& d, const RowTile& t, int zero_only) {
   T* __restrict__ f = static_cast<T*>(d.field);
-  const int64_t inner = d.inner, n = (int64_t)t.nrows * inner;
+  const int inner = (int)d.inner, nvec = UA ? (inner + V - 1) / V : inner / V;
   const T* __restrict__ bt = static_cast<const T*>(d.bval) + t.brow;
   const bool add_b = B && t.has_b && !zero_only;
-  for (int64_t e = threadIdx.x; e < n; e += blockDim.x) {
-    const int64_t r = e / inner, l = e - r * inner;
-    T v = T(0);
+  const int dr = 256 / nvec, dv = 256 - dr * nvec;
+  for (int r = (int)threadIdx.x / nvec, v = (int)threadIdx.x - r * nvec; r < t.nrows;) {
+    const int l = UA ? min(v * V, inner - V) : v * V;
+    Pack<T, V> y;
+#pragma unroll
+    for (int i = 0; i < V; ++i) y.v[i] = T(0);
     if (add_b) {
-      const T bb = bt[r * t.b_inner + (t.b_inner == 1 ? 0 : l)];
-      v = t.kind == SEG_VEC ? bb : v + bb;
+      Pack<T, V> bb;
+      if (t.b_inner == 1) {
+        const T b0 = bt[r];
+#pragma unroll
+        for (int i = 0; i < V; ++i) bb.v[i] = b0;
+      } else {
+        bb = ldv<T, V, true>(bt + (int64_t)r * t.b_inner + l);
+      }
+#pragma unroll
+      for (int i = 0; i < V; ++i) y.v[i] = t.kind == SEG_VEC ? bb.v[i] : y.v[i] + bb.v[i];
     }
-    f[(int64_t)d.row_dst[t.row_begin + r] * d.cs + l] = v;
+    stv<T, V, NT, UA>(f + (int64_t)d.row_dst[t.row_begin + r] * d.cs + l, y);
+    r += dr;
+    v += dv;
+    if (v >= nvec) {
+      v -= nvec;
+      ++r;
+    }
   }
 }
 
@@ -869,7 +891,8 @@ __global__ __launch_bounds__(256) void k_apply_win(PlanDesc d, const WinRun* __r
                                                    int nz, int gshift) {
   const int nwin = (nitems + 3) >> 2;
   if ((int)blockIdx.x >= nwin) {
-    for (int t = (int)blockIdx.x - nwin; t < nz; t += (int)gridDim.x - nwin) zero_row_tile<T, true>(d, ztiles[t], zero_only);
+    for (int t = (int)blockIdx.x - nwin; t < nz; t += (int)gridDim.x - nwin)
+      zero_row_tile<T, V, true, UA, true>(d, ztiles[t], zero_only);
     return;
   }
   // workgroups are dealt to the 8 XCDs round-robin: give each XCD a
@@ -948,7 +971,7 @@ __global__ __launch_bounds__(256) void k_apply_wide(PlanDesc d, const WideTile* 
   WideEnt<T>* le = reinterpret_cast<WideEnt<T>*>(wide_smem + (size_t)ucap * SB);  // ecap entries
   int32_t* lp = reinterpret_cast<int32_t*>(le + ecap);                                 // WIDE_ROWS + 1 row starts
   if ((int)blockIdx.x >= nwide) {  // a zero-row tile (no barrier is reached)
-    zero_row_tile<T, false>(d, ztiles[blockIdx.x - nwide], zero_only);
+    zero_row_tile<T, (V < 16 / (int)sizeof(T) ? V : 16 / (int)sizeof(T)), NT, false, false>(d, ztiles[blockIdx.x - nwide], zero_only);
     return;
   }
   // workgroups are dealt to the 8 XCDs round-robin: give each XCD a
@@ -1144,7 +1167,7 @@ __global__ __launch_bounds__(256) void k_apply_narrow(PlanDesc d, const NarrowTi
   constexpr int G = NARROW_LANES, IM = NARROW_ROW_BYTES / (int)sizeof(T);
   if (fs.n > 1) d.field = field_of(fs, (int)blockIdx.y);
   if ((int)blockIdx.x >= nnarrow) {  // a zero-row tile
-    zero_row_tile<T, true>(d, ztiles[blockIdx.x - nnarrow], zero_only);
+    zero_row_tile<T, 1, false, false, true>(d, ztiles[blockIdx.x - nnarrow], zero_only);
     return;
   }
   const NarrowTile tl = tiles[blockIdx.x];

@@ -216,3 +216,67 @@ def test_corner_rows_with_b_ride_in_the_strips_launch(rows, inner, dtype, ninner
     hb.apply_adjoint(plan, x)
     torch.cuda.synchronize()
     assert (x.view(6, W, W, inner)[:, :h] == 0).all()
+
+
+def one_strip_and_b(N, h, inner, ninner, rows):
+    """A cubed sphere's ghosts: matrix rows on one side of face 0 (4 consecutive
+    cells along the side, or their 4 x 4 square), b alone on every other side;
+    and the expected values as (box, values or None for the matrix rows)."""
+    p = hb.Program(hb.Grid.cubed_sphere(N, h))
+    rng = np.random.default_rng(inner)
+    W = N + 2 * h
+    J, I = (a.ravel() for a in np.meshgrid(np.arange(N), np.arange(-h, 0), indexing="ij"))
+    base = np.clip(J, 0, N - 4)
+    near = 1 if rows == "ell" else 4
+    cols = np.stack([(base + a + h) * W + (I + h if rows == "ell" else 0) + b + h
+                     for a in range(4) for b in range(near)], 1)
+    if rows == "ell":
+        p.add_ell([(0, 1), (0, N), (-h, 0)], 4, cols, np.full(cols.shape, 0.25))
+    else:
+        p.add_csr([(0, 1), (0, N), (-h, 0)], np.arange(len(J) + 1) * 16, cols, np.full(cols.shape, 1 / 16))
+    boxes = []
+    for f in range(6):
+        for box in ([(0, N), (-h, 0)], [(0, N), (N, N + h)], [(-h, 0), (0, N)], [(N, N + h), (0, N)]):
+            if f or box != [(0, N), (-h, 0)]:
+                v = rng.normal(size=(N * h, ninner))
+                p.add_vector([(f, f + 1)] + box, v, ninner=ninner)
+                boxes.append((f, box, v))
+    return p, boxes, cols
+
+
+# row vectors: whole and ending in a part, fewer and more than a workgroup's 256 threads
+@pytest.mark.parametrize("inner,dtype,rows", [(16, "f64", "ell"), (33, "f64", "ell"), (32, "f32", "ell"),
+                                              (137, "f32", "ell"), (1030, "f32", "ell"), (514, "f64", "ell"),
+                                              (1, "f64", "quad"), (3, "f32", "quad"), (64, "f64", "quad")])
+@pytest.mark.parametrize("scalar", [True, False])
+def test_most_rows_b_only(inner, dtype, rows, scalar):
+    dt, tdt = (hb.F64, torch.float64) if dtype == "f64" else (hb.F32, torch.float32)
+    N, h = 13, 3
+    p, boxes, cols = one_strip_and_b(N, h, inner, 1 if scalar else inner, rows)
+    plan = hb.Plan(p, inner=inner, dtype=dt)
+    x = torch.from_numpy(np.random.default_rng(1).integers(-8, 8, (p.grid.cells, inner))).to(tdt).cuda()
+    want = x.clone()
+    W = N + 2 * h
+    w6 = want.view(6, W, W, inner)
+    for f, (bj, bi), v in boxes:
+        side = torch.from_numpy(v).to(tdt).cuda().view(bj[1] - bj[0], bi[1] - bi[0], -1)
+        w6[f, bj[0] + h:bj[1] + h, bi[0] + h:bi[1] + h] = side
+    strip = x[torch.from_numpy(cols).cuda()].double().mean(1).to(tdt)  # small whole numbers: exact
+    w6[0, h:N + h, :h] = strip.view(N, h, inner)
+    hb.apply(plan, x)
+    torch.cuda.synchronize()
+    assert torch.equal(x, want)
+
+
+@pytest.mark.parametrize("N,inner", [(384, 32), (192, 137)])
+def test_most_rows_b_only_cost_no_more_than_the_row_kernel(N, inner):
+    """b-only rows that ride in the window launch take about the row kernel's
+    time (one value per lane took 1.5 to 2 times as long)."""
+    p, _, _ = one_strip_and_b(N, 3, inner, 1, "ell")
+    s = torch.cuda.Stream()
+    ms = []
+    for windows in (True, False):
+        plan = hb.Plan(p, inner=inner, dtype=hb.F32, windows=windows)
+        fields = [torch.zeros(plan.nelem, device="cuda") for _ in range(2)]
+        ms.append(min(hb.time_apply(plan, fields, 40, s.cuda_stream) for _ in range(9)))
+    assert ms[0] <= 1.25 * ms[1]
