@@ -147,8 +147,9 @@ typedef struct {
 /* Launch shape of the apply kernels (chosen by the plan, changed by tuning).
  * The staged point-major adjoints and the plane-major adjoint have fixed shapes
  * of their own; the point-major CSR-walking adjoint follows this one.
- * Plane-major plans take one row per lane: lanes_per_row does not apply, and
- * rows_per_tile only to rows of more than four entries. */
+ * Plane-major plans whose rows all have at most four entries take one row per
+ * lane: lanes_per_row and rows_per_tile do not apply; in the others
+ * lanes_per_row sets of lanes share a tile's rows, each with planes of its own. */
 typedef struct {
   int32_t block;            /* threads per workgroup: 64, 128, 192 or 256 */
   int32_t lanes_per_row;    /* power of two; lanes that share one row */

@@ -421,7 +421,8 @@ struct HostTables {
   // narrow wide rows (see NarrowTile); seg_narrow marks the segments they take
   std::vector<char> seg_narrow;
   std::vector<NarrowTile> ntiles;
-  // plane-major rows of few entries (see PLANE_ROWS); seg_plane marks the segments they take
+  // plane-major rows of few entries (see PlanePiece); seg_plane marks the segments they take
+  size_t pm_tiles = 0;  // tiles of the other segments, before those of the pieces' rows
   std::vector<char> seg_plane;
   int32_t p_me = 1;                // entries per row of the table (1 or PLANE_ME)
   int32_t p_rows = 64;             // rows per piece at most

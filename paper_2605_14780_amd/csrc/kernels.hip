@@ -195,18 +195,18 @@ __device__ __forceinline__ int64_t rot_slot(const PlanDesc& d, int rot, int64_t 
   return d.vec_lo + p * d.vec_stride + off;
 }
 
-// Plane-major tile of a general ELL/CSR segment s: rows [row0, row0 + nrows),
-// planes [p0, p0 + np), np <= PB.  The lanes take consecutive rows
+// Plane-major tile of a segment s: rows [row0, row0 + nrows), planes
+// [p0, p0 + np), np <= PB.  The lanes take consecutive rows
 // (neighbouring ghost cells are neighbours in every plane); a lane reads each
-// entry once for the PB planes, and issues its loads of all of them before any
-// arithmetic.  The planes are the same for every lane, so their bases and
-// rotations are scalar.
-constexpr int PB = 8;
-
-template <typename T>
+// entry once for its planes, and issues its loads of all of them before any
+// arithmetic.  Plain stores: strips of a slow index write pieces of a line
+// whose rest another tile writes, which non-temporal stores send to memory
+// apart (the adjoint's zero pass at C384 x 64 FP64 14 us slower).
+template <typename T, int PB>
 __device__ __forceinline__ void run_tile_pm(const PlanDesc& d, const DevSeg& s, int row0, int nrows, int64_t p0,
                                             int np, bool zero_only, int r0, int rstep) {
   T* __restrict__ f = static_cast<T*>(d.field);
+  const bool sum = !zero_only && s.kind != SEG_ZERO && s.kind != SEG_VEC;
   T* out[PB];
   const T* in[PB];
   T sign[PB];
@@ -214,7 +214,7 @@ __device__ __forceinline__ void run_tile_pm(const PlanDesc& d, const DevSeg& s, 
   for (int u = 0; u < PB; ++u) {
     const int64_t l = p0 + min(u, np - 1);
     out[u] = f + l * d.ls;
-    in[u] = f + rot_slot<T>(d, s.rot, l, sign[u]) * d.ls;
+    in[u] = f + rot_slot<T>(d, sum ? s.rot : 0, l, sign[u]) * d.ls;
   }
   for (int r = r0; r < nrows; r += rstep) {
     const int64_t row = (int64_t)row0 + r;
@@ -222,7 +222,16 @@ __device__ __forceinline__ void run_tile_pm(const PlanDesc& d, const DevSeg& s, 
     T y[PB];
 #pragma unroll
     for (int u = 0; u < PB; ++u) y[u] = T(0);
-    if (!zero_only) {
+    if (sum && s.kind == SEG_MAP) {
+      const int64_t c = d.row_src[s.row_base + row];
+      T x[PB];
+#pragma unroll
+      for (int u = 0; u < PB; ++u)
+        if (u < np) x[u] = in[u][c];
+#pragma unroll
+      for (int u = 0; u < PB; ++u)
+        if (u < np) y[u] = sign[u] * (T(s.w) * x[u]);
+    } else if (sum) {
       int64_t e0, e1;
       const int32_t* cols;
       const T* vals;
@@ -251,16 +260,21 @@ __device__ __forceinline__ void run_tile_pm(const PlanDesc& d, const DevSeg& s, 
           if (u < np) y[u] = first ? w * x[u] : fma(w, x[u], y[u]);
         first = false;
       }
+#pragma unroll
+      for (int u = 0; u < PB; ++u) y[u] = sign[u] * y[u];
+    }
+    if (!zero_only && s.has_b) {
       const T* bp = static_cast<const T*>(d.bval) + s.brow + row * s.b_inner;
 #pragma unroll
-      for (int u = 0; u < PB; ++u) {
-        y[u] = sign[u] * y[u];
-        if (s.has_b && u < np) y[u] = y[u] + (s.b_inner == 1 ? bp[0] : bp[p0 + u]);
-      }
+      for (int u = 0; u < PB; ++u)
+        if (u < np) {
+          const T bb = s.b_inner == 1 ? bp[0] : bp[p0 + u];
+          y[u] = s.kind == SEG_VEC ? bb : y[u] + bb;
+        }
     }
 #pragma unroll
     for (int u = 0; u < PB; ++u)
-      if (u < np) __builtin_nontemporal_store(y[u], &out[u][dst]);
+      if (u < np) out[u][dst] = y[u];
   }
 }
 
@@ -1311,17 +1325,28 @@ __device__ __forceinline__ int plane_item(int it, int items) {
   return x * q + min(x, rem) + (it >> 3);
 }
 
-// Rows of general width, by segment tiles.
-template <typename T>
+// Rows of more than PLANE_ME entries (and those beside them, see plane_tiles),
+// by segment tiles.  The threads of a workgroup are sets of lanes with a row
+// each; set k takes planes p0 + k np ... of the group, so that a tile's
+// entries are read into one L1 for all of them.  Bound by the round trips of a
+// row's entries, one after another, and by the lines its sources touch; the
+// shape is default_tune's.  C192 FP64 quadrature rows (22 entries), one
+// workgroup per tile over all planes, one row per lane and 8 planes a
+// workgroup (tiles dealt out twice), and so: 1 plane 23.6, 19.0 and 8.9 us, 9
+// planes 33.6, 34.4 and 17.4, 100 planes 162, 190 and 148, 256 planes 450, 464
+// and 350.
+template <typename T, int PB>
 __global__ __launch_bounds__(256) void k_apply_pm(PlanDesc d, const DevTile* __restrict__ tiles, int ntiles,
-                                                  int items, int zero_only) {
+                                                  int items, int np, int zero_only) {
   for (int it = blockIdx.x; it < items; it += gridDim.x) {
     const int item = plane_item(it, items), pg = item / ntiles, t = item - pg * ntiles;
-    const int64_t p0 = (int64_t)pg * PB;
+    const int rp = (int)blockDim.x >> d.lpr_shift, set = (int)threadIdx.x / rp;
+    const int64_t p0 = (((int64_t)pg << d.lpr_shift) + set) * np;
+    if (set >> d.lpr_shift || p0 >= d.inner) continue;
     const DevTile tl = tiles[t];
     const DevSeg s = d.segs[tl.seg];
-    run_tile_pm<T>(d, s, (int)tl.row0, tl.nrows, p0, (int)min<int64_t>(PB, d.inner - p0), zero_only != 0,
-                   (int)threadIdx.x, (int)blockDim.x);
+    run_tile_pm<T, PB>(d, s, (int)tl.row0, tl.nrows, p0, (int)min<int64_t>(np, d.inner - p0), zero_only != 0,
+                   (int)threadIdx.x - set * rp, rp);
   }
 }
 
@@ -3119,11 +3144,25 @@ static void launch_fixed(const Plan& p, const PlanDesc& d, hipStream_t st, bool 
     launch_fixed_hb<T, false>(p, d, st, z, nz);
 }
 
-// Plane-major plans: the rows of few entries, then the tiles of the others.
+constexpr int PM_PLANES = 8;  // planes per lane of the segment tiles at most
+
+// Planes per set of lanes, evenly many in every set (9 planes on 2 sets as
+// 5 + 4 rather than 8 + 1).
+static int64_t pm_planes(const Plan& p) {
+  const int64_t I = p.layout.inner, S = p.tune.lanes_per_row;
+  const int64_t groups = (I + PM_PLANES * S - 1) / (PM_PLANES * S);
+  return (I + groups * S - 1) / (groups * S);
+}
+
+// Plane-major plans: the rows of few entries by pieces, the others by tiles;
+// every row by tiles where all of them only are zeroed.
 template <typename T>
 static void launch_planes(const Plan& p, const PlanDesc& d, hipStream_t st, int z) {
-  const int64_t rows = (p.layout.inner + PLANE_PB - 1) / PLANE_PB * (int64_t)p.host.p_pieces.size();
-  const int64_t tiles = (p.layout.inner + PB - 1) / PB * (int64_t)p.host.tiles.size();
+  const int nt = (int)(z ? p.host.tiles.size() : p.host.pm_tiles);
+  const int64_t pieces = z && nt > 0 ? 0 : (int64_t)p.host.p_pieces.size();
+  const int64_t rows = (p.layout.inner + PLANE_PB - 1) / PLANE_PB * pieces;
+  const int64_t np = pm_planes(p), S = p.tune.lanes_per_row;
+  const int64_t tiles = (p.layout.inner + np * S - 1) / (np * S) * nt;
   if (std::max(rows, tiles) >= (int64_t(1) << 31)) fail(HBC_EUNSUPPORTED, "plane-major apply too large for one launch");
   auto grid = [&](int64_t n) { return dim3((unsigned)(p.tune.persistent > 0 ? std::min<int64_t>(p.tune.persistent, n) : n)); };
   const dim3 blk(p.tune.block);
@@ -3146,7 +3185,17 @@ static void launch_planes(const Plan& p, const PlanDesc& d, hipStream_t st, int 
     HIP_CHECK(hipGetLastError());
   }
   if (tiles > 0) {
-    HBC_LAUNCH((k_apply_pm<T>), grid(tiles), blk, 0, st, d, p.d_tiles, (int)p.host.tiles.size(), (int)tiles, z);
+    auto run = [&](auto pb) {
+      HBC_LAUNCH((k_apply_pm<T, decltype(pb)::value>), grid(tiles), blk, 0, st, d, p.d_tiles, nt, (int)tiles, (int)np, z);
+    };
+    if (np > 4)
+      run(std::integral_constant<int, PM_PLANES>{});
+    else if (np > 2)
+      run(std::integral_constant<int, 4>{});
+    else if (np > 1)
+      run(std::integral_constant<int, 2>{});
+    else
+      run(std::integral_constant<int, 1>{});
     HIP_CHECK(hipGetLastError());
   }
 }
@@ -4090,8 +4139,8 @@ void device_batch_stats(const Batch* b, hbc_stats* out) { *out = b->stats; }
 // a choice stored by a build whose kernels time differently is not reused
 // (bumped with such changes; 2: window loads at raised priority, where runs
 // of 4 turned from the fastest to among the slowest; 3: plane-major pieces,
-// short windows, windows in batches).
-constexpr int TUNE_CACHE_GEN = 3;
+// short windows, windows in batches; 4: plane-major tiles by sets of planes).
+constexpr int TUNE_CACHE_GEN = 4;
 
 static std::string batch_key(const Batch* b) {
   int dev = 0;

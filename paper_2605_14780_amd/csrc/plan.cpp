@@ -837,6 +837,41 @@ static int32_t plane_rows(const Plan& plan) {
   return n;
 }
 
+// Entries of a segment's longest row.
+static int64_t longest_row(const HostTables& T, const DevSeg& sg) {
+  if (sg.kind == SEG_MAP) return 1;
+  if (sg.kind == SEG_ELL) return sg.width;
+  int64_t most = 0;
+  if (sg.kind == SEG_CSR)
+    for (int64_t r = 0; r < sg.nrows; ++r)
+      most = std::max(most, T.csr_ptr[sg.tab + r + 1] - T.csr_ptr[sg.tab + r]);
+  return most;
+}
+
+// Which rows of a plane-major plan go by segment tiles: none, those of the
+// segments with a row of more than PLANE_ME entries, or all.  Pieces beside
+// tiles are a second launch, which costs 2 us (C12 to C48 quadrature rows with
+// zero corners 10-34 % of the apply) and pays where many rows of few entries
+// have many planes: C384 FP64, 12 sides of 4-point rows (9216) beside 12 of 16
+// entries, 64 planes 48 us all by tiles and 43 with pieces (100 planes 102 and
+// 74, 24 planes 21.0 and 20.1); C97 with 23 sides of them (6693) 100 planes
+// 15.8 and 22.7; C384 with 23 (17664) 24 planes 12.5 and 14.3, 100 planes 35
+// and 32, 256 planes FP32 91 and 51.
+enum PlaneTiles { TILES_NONE, TILES_WIDE, TILES_ALL };
+static PlaneTiles plane_tiles(const Plan& plan) {
+  bool wide = false;
+  int64_t few = 0;  // matrix rows of few entries
+  for (const DevSeg& sg : plan.host.segs) {
+    const int64_t most = longest_row(plan.host, sg);
+    if (most > PLANE_ME)
+      wide = true;
+    else if (most > 0)
+      few += sg.nrows;
+  }
+  if (!wide) return TILES_NONE;
+  return few >= 8192 && plan.layout.inner >= 32 ? TILES_WIDE : TILES_ALL;
+}
+
 hbc_tune default_tune(const Plan& plan) {
   hbc_tune t{};
   t.block = 256;
@@ -848,6 +883,21 @@ hbc_tune default_tune(const Plan& plan) {
     int64_t nvec = plan.layout.inner / plan.vec;
     int64_t nacc = (nvec + plan.unroll - 1) / plan.unroll;
     t.lanes_per_row = (int32_t)std::min<int64_t>(t.block, pow2_ceil(nacc));
+  } else if (plane_tiles(plan) != TILES_NONE) {
+    // sets of planes per workgroup: 16 up to 32 planes (fewer of the fewest),
+    // which alone fill few workgroups; beyond, 4, or 1 beside pieces.  Of the
+    // time with one workgroup per tile over all planes (C12 to C384, FP64 and
+    // FP32, quadrature rows alone and beside strips, means): 16 planes 0.46
+    // with 16 sets and 0.60 with 4, 32 planes 0.57 and 0.82, 100 planes 0.86
+    // and 0.77, 256 planes 0.69 and 0.55.  Large FP32 plans take 1 set from 32
+    // planes on: quadrature rows, C384 x 64 119 us (4 sets 155), C192 x 64 64
+    // (78), but C192 x 100 FP64 186 (148).
+    t.block = 128;
+    const int64_t I = plan.layout.inner;
+    t.lanes_per_row = (int32_t)std::min<int64_t>(16, std::max<int64_t>(4, pow2_ceil(I)));
+    const bool mixed = plane_tiles(plan) == TILES_WIDE;
+    if (I > 32) t.lanes_per_row = mixed ? 1 : 4;
+    if (I >= 32 && !mixed && plan.dtype == HBC_F32 && rows >= 8192) t.lanes_per_row = 1;
   } else {
     // plane-major: one row per lane; at least two wavefronts to stage a piece
     t.lanes_per_row = 1;
@@ -860,7 +910,7 @@ hbc_tune default_tune(const Plan& plan) {
   // in all.
   int64_t rpt;
   if (plan.layout.order != HBC_POINT_MAJOR) {
-    rpt = rows_per_pass;  // one row per lane
+    rpt = rows_per_pass;  // one row per lane or set of lanes
   } else if (t.lanes_per_row >= CHUNK_LPR) {
     rpt = rows_per_pass * rows_per_batch(t.lanes_per_row);
   } else {
@@ -1021,18 +1071,15 @@ static void build_narrow(Plan& plan) {
 static void build_planes(Plan& plan) {
   HostTables& T = plan.host;
   T.seg_plane.assign(T.segs.size(), 0);
-  if (plan.layout.order != HBC_PLANE_MAJOR) return;
+  const PlaneTiles tiles = plane_tiles(plan);
+  if (plan.layout.order != HBC_PLANE_MAJOR || tiles == TILES_ALL) return;
   std::vector<uint64_t> rows;  // destination cell << 32 | row
   std::vector<int32_t> seg_of(T.row_dst.size(), -1);
   auto dst_of = [](uint64_t k) { return (int64_t)(k >> 32); };
   T.p_me = 1;
   for (size_t si = 0; si < T.segs.size(); ++si) {
     const DevSeg& sg = T.segs[si];
-    int64_t most = sg.kind == SEG_MAP ? 1 : 0;
-    if (sg.kind == SEG_ELL) most = sg.width;
-    if (sg.kind == SEG_CSR)
-      for (int64_t r = 0; r < sg.nrows; ++r)
-        most = std::max(most, T.csr_ptr[sg.tab + r + 1] - T.csr_ptr[sg.tab + r]);
+    const int64_t most = longest_row(T, sg);
     if (most > PLANE_ME) continue;
     T.seg_plane[si] = 1;
     if (most > 1) T.p_me = PLANE_ME;
@@ -1259,23 +1306,29 @@ void build_tiles(Plan& plan, const hbc_tune& t) {
   if (t.window_order != 0 && t.window_order != 1) fail(HBC_EINVAL, "window_order must be 0 or 1");
   if (plan.host.seg_plane.size() != plan.host.segs.size()) build_planes(plan);
   std::vector<DevTile> tiles;
-  for (size_t s = 0; s < plan.host.segs.size(); ++s) {
-    const DevSeg& sg = plan.host.segs[s];
-    if (plan.host.seg_plane[s]) continue;  // served by the plane-row kernel
-    for (int64_t r0 = 0; r0 < sg.nrows; r0 += t.rows_per_tile) {
-      DevTile tl;
-      tl.seg = (int32_t)s;
-      tl.nrows = (int32_t)std::min<int64_t>(t.rows_per_tile, sg.nrows - r0);
-      tl.row0 = r0;
-      tiles.push_back(tl);
+  auto cut = [&](char plane) {  // the segments whose rows the pieces take, or the others
+    for (size_t s = 0; s < plan.host.segs.size(); ++s) {
+      const DevSeg& sg = plan.host.segs[s];
+      if (plan.host.seg_plane[s] != plane) continue;
+      for (int64_t r0 = 0; r0 < sg.nrows; r0 += t.rows_per_tile) {
+        DevTile tl;
+        tl.seg = (int32_t)s;
+        tl.nrows = (int32_t)std::min<int64_t>(t.rows_per_tile, sg.nrows - r0);
+        tl.row0 = r0;
+        tiles.push_back(tl);
+      }
     }
-  }
+  };
+  cut(0);
+  plan.host.pm_tiles = tiles.size();
+  if (!tiles.empty()) cut(1);  // for the adjoint's zero pass, which takes one launch
   // Workgroups are dealt to the 8 XCDs round-robin; interleave so that each
   // XCD walks a contiguous run of tiles (neighbouring rows share sources).
+  // (Plane-major launches deal out (plane group, tile) items themselves.)
   const size_t n = tiles.size();
   std::vector<DevTile> out(n);
   const size_t X = 8;
-  if (n >= X * 2) {
+  if (n >= X * 2 && plan.layout.order == HBC_POINT_MAJOR) {
     size_t per = (n + X - 1) / X;
     size_t i = 0;
     for (size_t k = 0; k < per * X; ++k) {
@@ -1287,7 +1340,7 @@ void build_tiles(Plan& plan, const hbc_tune& t) {
     out = tiles;
   }
   plan.host.tiles.swap(out);
-  plan.stats.tiles = (int64_t)plan.host.tiles.size() + (int64_t)plan.host.p_pieces.size();
+  plan.stats.tiles = (int64_t)plan.host.pm_tiles + (int64_t)plan.host.p_pieces.size();
   plan.tune = t;
   // the same cut as point-major row tiles (same XCD-aware order)
   plan.host.rtiles.clear();
