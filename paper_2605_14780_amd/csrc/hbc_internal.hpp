@@ -352,6 +352,14 @@ struct AdjLdsHost {
 constexpr int ADJW_SRC = 256, ADJW_UCAP = 256, ADJW_ECAP = 1024, ADJW_LANES = 16;
 constexpr int ADJW_SPG = 4;                  // sources per row group at most
 constexpr int ADJW_ROW_BYTES = 128;          // plans of few entries per source: rows from here on
+// to here, or to here where most sources have one entry.  Long rows fill the
+// other kernels' workgroups by themselves, and a row of one reader gains
+// nothing from the stage (the other kernels against this one, C48 h 3):
+// 4-point rows FP64 x 1024 90 and 45 us, x 1026 50 and 46, x 1025 53 and 80,
+// x 4096 146 and 197, FP32 x 2048 90 and 44, x 4096 91 and 93; copies FP64
+// x 384 16.0 and 15.5, x 512 20.0 and 20.8 (C97 h 2 20 and 25), x 1024 35 and
+// 42, x 4096 96 and 192, FP32 x 1025 57 and 72.
+constexpr int ADJW_LONG_BYTES = 8192, ADJW_COPY_BYTES = 3072;
 // tiles are kept short enough for about 3 workgroups per CU: FP64 C768 x 32
 // 10.1 us with 768, 10.6 with 512, 13.9 with 1024 (two rounds of workgroups)
 constexpr int ADJW_ITEMS = 768;

@@ -1455,7 +1455,10 @@ static void build_adj_wide(Plan& plan, int64_t maxc) {
   const Layout& L = plan.layout;
   if (L.order != HBC_POINT_MAJOR || L.inner > (int64_t(1) << 30)) return;
   const int64_t es = plan.dtype == HBC_F64 ? 8 : 4;
-  if (maxc <= ADJ_MAXW && L.inner * es < ADJW_ROW_BYTES) return;
+  const bool copies = C.w.size() < 2 * C.src_cell.size();
+  if (maxc <= ADJ_MAXW &&
+      (L.inner * es < ADJW_ROW_BYTES || L.inner * es > (copies ? ADJW_COPY_BYTES : ADJW_LONG_BYTES)))
+    return;
   const int64_t nvec = L.inner / plan.vec;
   while ((1 << A.lanes_shift) < std::min<int64_t>(nvec, ADJW_LANES)) ++A.lanes_shift;
   const int64_t lanes = int64_t(1) << A.lanes_shift, slice = lanes * plan.vec;

@@ -30,3 +30,32 @@ def test_unread_ghost_rows_are_zeroed(inner, nzero):
     torch.cuda.synchronize()
     want = [0.0] * (nzero + 1) + [5.5, 1.0]
     assert [float(r.min()) for r in x] == want and [float(r.max()) for r in x] == want
+
+
+def copies(n, inner, dtype, fan=1):
+    """Ghost k of n copies cell k // fan of a 1-D block."""
+    g = hb.Grid([0], [2 * n])
+    g.add_block([(0, 2 * n)], [(n, 2 * n)])
+    p = hb.Program(g)
+    p.add_csr([(0, n)], np.arange(n + 1), n + np.arange(n) // fan, np.ones(n))
+    return hb.Plan(p, inner=inner, dtype=dtype)
+
+
+# the row lengths at which plans of few entries per source take another kernel:
+# 128 bytes, 3 KiB where most sources have one entry, 8 KiB
+@pytest.mark.parametrize("inner,fan,wide", [(15, 1, False), (16, 1, True), (384, 1, True), (385, 1, False),
+                                            (1024, 4, True), (1026, 4, False), (4097, 4, False)])
+def test_rows_of_every_length_take_a_kernel_and_sum_right(inner, fan, wide):
+    """Small whole numbers: every order of a sum gives the same value."""
+    n = 70
+    plan = copies(n, inner, hb.F64, fan)
+    assert any("k_adjoint_wide" in k for k in plan.kernels(hb.OP_ADJOINT)) == wide
+    x = torch.randint(-9, 9, (2 * n, inner), device="cuda", generator=torch.Generator("cuda").manual_seed(inner)).double()
+    want = x.clone()
+    want[:n] = 0
+    want.index_add_(0, n + torch.arange(n, device="cuda") // fan, x[:n])
+    for call in (hb.apply_adjoint, hb.apply_adjoint_noalloc):
+        got = x.clone()
+        call(plan, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
