@@ -157,7 +157,7 @@ typedef struct {
   int32_t persistent;       /* 0: one workgroup per tile; >0: that many workgroups loop over tiles */
   int32_t window_order;     /* sliding-window rows: 0 pipelined (each row's store issued while later
                                rows' sources still arrive), 1 ordered (sources, then the rows in turn);
-                               both give the same bits */
+                               both give the same bits; rows of at most 512 bytes have one order */
 } hbc_tune;
 
 /* ---- errors ---------------------------------------------------------------- */

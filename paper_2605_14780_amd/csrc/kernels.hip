@@ -3216,6 +3216,17 @@ static bool small_apply(const Plan& p) {
   return T.rtiles.size() + T.ntiles.size() < 2 * 256;
 }
 
+// Whether the row tiles ride in the first wide-row, narrow or window launch:
+// all zero or b-only rows (the corners of the cubed-sphere programs), in a
+// launch that carries b if they do.
+static bool rows_ride(const Plan& p) {
+  const HostTables& T = p.host;
+  if (p.layout.order != HBC_POINT_MAJOR || T.rtiles.empty() || !T.rt_light) return false;
+  if (!T.ntiles.empty()) return true;
+  if (!T.wtiles.empty()) return !T.rt_light_b;
+  return !T.wruns.empty() || !T.fruns.empty();
+}
+
 template <typename T>
 static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, bool zero_only,
                            const FieldSet& fs = FieldSet{}) {
@@ -3231,12 +3242,9 @@ static void launch_apply_t(const Plan& p, const PlanDesc& d, hipStream_t st, boo
     dd.nrows = (int32_t)p.stats.rows_data;
     dd.grid = (int32_t)std::min<int64_t>((p.stats.rows_data + groups - 1) / groups, 4096);
   }
-  // fold the row tiles into the first wide-row or window launch when they are
-  // all zero or b-only rows (the corners of the cubed-sphere programs)
   const bool has_narrow = pm && !p.host.ntiles.empty(), has_wide = pm && !p.host.wtiles.empty();
   const bool has_win = pm && !p.host.wruns.empty(), has_fixed = pm && !p.host.fruns.empty();
-  const bool fold = (has_narrow || has_wide || has_win || has_fixed) && dd.grid == 0 && nt > 0 && p.host.rt_light &&
-                    (has_narrow || !has_wide || !p.host.rt_light_b);
+  const bool fold = dd.grid == 0 && rows_ride(p);
   if (has_narrow) {
     const int nn = (int)p.host.ntiles.size();
     HBC_LAUNCH((k_apply_narrow<T>), dim3(nn + (fold ? nt : 0), fs.n), dim3(256), 0, st, d, p.d_ntiles, z,
@@ -4197,7 +4205,9 @@ static std::string plan_key(const Plan& p) {
   k << prop.gcnArchName << "|g" << TUNE_CACHE_GEN << "|plan|" << (p.dtype == HBC_F64 ? "f64" : "f32") << "|"
     << (p.layout.order == HBC_POINT_MAJOR ? "point" : "plane") << "|" << p.layout.inner << "|" << p.vec << "|"
     << p.stats.rows_covered << "|" << p.stats.segments << "|" << p.stats.nnz << "|" << p.stats.rows_data << "|w"
-    << (windows_possible(p) ? 1 : 0);
+    << (windows_possible(p) ? 1 : 0) << (p.host.fruns.empty() ? "" : "f")
+    << (p.flags & HBC_PLAN_NO_WINDOWS ? "n" : "") << "|b" << p.stats.rows_with_b << "|p"
+    << p.host.p_pieces.size() << "|" << (p.host.pm_tiles > 0 ? 1 : 0);
   std::string s = k.str();
   for (char& c : s)
     if (c == '"' || c == '\\') c = '_';
@@ -4237,11 +4247,19 @@ double device_plan_autotune(Plan& p, void* const* fields, int nfields, const cha
     // number of wavefronts in flight) and the order of loads and stores
     for (int r : {4, 6, 8, 10, 12, 16})
       for (int o : {0, 1}) {
+        if (o && win_short_shift(row_vectors(p)) < 6) continue;  // short rows have one order
         hbc_tune t = def;
         t.rows_per_tile = r;
         t.window_order = o;
         cand.push_back(t);
       }
+  } else if (p.layout.order == HBC_PLANE_MAJOR && p.host.pm_tiles == 0) {
+    // pieces alone: one row per lane, whatever the lanes and rows of the shape
+    for (int bl : {128, 256})
+      for (int pf : {0, 4}) cand.push_back(hbc_tune{bl, def.lanes_per_row, def.rows_per_tile, pf * ncu});
+  } else if (p.stats.rows_data == 0 && rows_ride(p)) {
+    // wide, narrow and fixed runs with zero and b-only rows beside them: the
+    // shape cuts those few only
   } else {
     for (int bl : {128, 256})
       for (int lf : {1, 2}) {
