@@ -59,3 +59,47 @@ def test_rows_of_every_length_take_a_kernel_and_sum_right(inner, fan, wide):
         call(plan, got)
         torch.cuda.synchronize()
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("inner,dtype", [(5, "f64"), (32, "f32"), (301, "f64")])
+def test_source_of_more_ghosts_than_a_tile_stages(inner, dtype):
+    """One cell that 300 ghosts read: the plan goes by the walking kernel,
+    point-major, with and without allocation."""
+    n, tdt = 300, torch.float64 if dtype == "f64" else torch.float32
+    plan = copies(n, inner, hb.F64 if dtype == "f64" else hb.F32, fan=n)
+    assert any("k_adjoint<" in k for k in plan.kernels(hb.OP_ADJOINT))
+    x = torch.randint(-9, 9, (2 * n, inner), device="cuda", generator=torch.Generator("cuda").manual_seed(1)).to(tdt)
+    want = x.clone()
+    want[:n] = 0
+    want[n] += x[:n].sum(0)
+    for call in (hb.apply_adjoint, hb.apply_adjoint_noalloc):
+        got = x.clone()
+        call(plan, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+
+
+# reader counters (shared rows x slices of 16 values) beyond the static array's
+# 2^20: sources of 16 entries in long rows, of 2 in many rows
+@pytest.mark.parametrize("n,entries,inner", [(200, 16, 84001), (9000, 2, 2047)])
+def test_noalloc_without_room_for_the_counters(n, entries, inner):
+    """The allocation-free call takes another kernel, with the same bits, on
+    repeated calls too."""
+    g = hb.Grid([0], [2 * n])
+    g.add_block([(0, 2 * n)], [(n, 2 * n)])
+    p = hb.Program(g)
+    cols = (np.arange(n)[:, None] + np.arange(entries) * (n // entries)) % n
+    p.add_csr([(0, n)], np.arange(n + 1) * entries, n + cols, np.ones((n, entries)))
+    plan = hb.Plan(p, inner=inner, dtype=hb.F32)
+    assert any("k_adjoint_wide" in k for k in plan.kernels(hb.OP_ADJOINT))
+    gen = torch.Generator("cuda").manual_seed(n)
+    x = torch.randint(-9, 9, (2 * n, inner), device="cuda", generator=gen, dtype=torch.int32).float()
+    want = x.clone()  # small whole numbers: exact in any order
+    want[:n] = 0
+    for m in range(entries):
+        want[n:].index_add_(0, torch.from_numpy(cols[:, m]).cuda(), x[:n])
+    for call in (hb.apply_adjoint, hb.apply_adjoint_noalloc, hb.apply_adjoint_noalloc, hb.apply_adjoint):
+        got = x.clone()
+        call(plan, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
