@@ -81,14 +81,15 @@ def test_source_of_more_ghosts_than_a_tile_stages(inner, dtype):
 
 # reader counters (shared rows x slices of 16 values) beyond the static array's
 # 2^20: sources of 16 entries in long rows, of 2 in many rows
-@pytest.mark.parametrize("n,entries,inner", [(200, 16, 84001), (9000, 2, 2047)])
+@pytest.mark.parametrize("n,entries,inner", [(200, 16, 100001), (12000, 2, 2047)])
 def test_noalloc_without_room_for_the_counters(n, entries, inner):
     """The allocation-free call takes another kernel, with the same bits, on
     repeated calls too."""
     g = hb.Grid([0], [2 * n])
     g.add_block([(0, 2 * n)], [(n, 2 * n)])
     p = hb.Program(g)
-    cols = (np.arange(n)[:, None] + np.arange(entries) * (n // entries)) % n
+    k = np.arange(n)[:, None]  # the second cell of two: another tile's, for nearly every ghost
+    cols = np.hstack([k, k * 4801 % n]) if entries == 2 else (k + np.arange(entries) * (n // entries)) % n
     p.add_csr([(0, n)], np.arange(n + 1) * entries, n + cols, np.ones((n, entries)))
     plan = hb.Plan(p, inner=inner, dtype=hb.F32)
     assert any("k_adjoint_wide" in k for k in plan.kernels(hb.OP_ADJOINT))
