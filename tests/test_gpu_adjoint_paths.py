@@ -80,16 +80,20 @@ def test_source_of_more_ghosts_than_a_tile_stages(inner, dtype):
 
 
 # reader counters (shared rows x slices of 16 values) beyond the static array's
-# 2^20: sources of 16 entries in long rows, of 2 in many rows
-@pytest.mark.parametrize("n,entries,inner", [(200, 16, 100001), (12000, 2, 2047)])
+# 2^20: sources of 16 entries in long rows (the walking kernel's), of 8 in many
+# rows (the LDS kernel's)
+@pytest.mark.parametrize("n,entries,inner", [(200, 16, 100001), (16000, 2, 1279)])
 def test_noalloc_without_room_for_the_counters(n, entries, inner):
     """The allocation-free call takes another kernel, with the same bits, on
     repeated calls too."""
     g = hb.Grid([0], [2 * n])
     g.add_block([(0, 2 * n)], [(n, 2 * n)])
     p = hb.Program(g)
-    k = np.arange(n)[:, None]  # the second cell of two: another tile's, for nearly every ghost
-    cols = np.hstack([k, k * 4801 % n]) if entries == 2 else (k + np.arange(entries) * (n // entries)) % n
+    k, m = np.arange(n)[:, None], n // 4
+    if entries == 2:  # four times as many ghosts as sources: nearly every ghost has sources of two tiles
+        cols = np.hstack([k % m, (k * 4801 + k // m * 17) % m])
+    else:
+        cols = (k + np.arange(entries) * (n // entries)) % n
     p.add_csr([(0, n)], np.arange(n + 1) * entries, n + cols, np.ones((n, entries)))
     plan = hb.Plan(p, inner=inner, dtype=hb.F32)
     assert any("k_adjoint_wide" in k for k in plan.kernels(hb.OP_ADJOINT))
@@ -97,8 +101,8 @@ def test_noalloc_without_room_for_the_counters(n, entries, inner):
     x = torch.randint(-9, 9, (2 * n, inner), device="cuda", generator=gen, dtype=torch.int32).float()
     want = x.clone()  # small whole numbers: exact in any order
     want[:n] = 0
-    for m in range(entries):
-        want[n:].index_add_(0, torch.from_numpy(cols[:, m]).cuda(), x[:n])
+    for c in cols.T:
+        want[n:].index_add_(0, torch.from_numpy(c).cuda(), x[:n])
     for call in (hb.apply_adjoint, hb.apply_adjoint_noalloc, hb.apply_adjoint_noalloc, hb.apply_adjoint):
         got = x.clone()
         call(plan, got)
