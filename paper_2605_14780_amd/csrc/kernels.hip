@@ -57,6 +57,7 @@ struct PlanDesc {
   int32_t general;    // the row tiles hold general ELL/CSR rows
   int32_t ua;         // point-major rows as 16-byte vectors on 4-byte (FP32) or 8-byte (FP64)
                       // boundaries, the last one ending at the row's end (see rt_tile)
+  int32_t nfields;    // fields of this launch (see FieldSet), at most 1: `field`
   const int32_t* row_dst;  // point-major row tables
   const int32_t* row_src;
 };
@@ -82,12 +83,14 @@ __device__ __forceinline__ T* as_global(T* p) {
 }
 
 // Several fields in one launch (k_apply_rows, k_apply_narrow): grid row y takes
-// p[y] instead of the descriptor's field.  They travel in the kernel's
+// p[y] instead of the descriptor's field.  Their number is in the descriptor: a
+// launch of one field that reads this line of its arguments takes 0.2 us longer
+// (C98 strips of 3 values 3.86 -> 4.02 us).  They travel in the kernel's
 // arguments: a table in device memory would have to be allocated, copied and
 // freed beside captures that the caller may have open.
 constexpr int FIELDS_PER_LAUNCH = 8;
 struct FieldSet {
-  int32_t n = 1;
+  int32_t n = 1;  // (on the host)
   void* p[FIELDS_PER_LAUNCH] = {};
 };
 __device__ __forceinline__ void* field_of(const FieldSet& fs, int y) {
@@ -1179,7 +1182,7 @@ __global__ __launch_bounds__(256) void k_apply_narrow(PlanDesc d, const NarrowTi
                                                       int zero_only, const RowTile* __restrict__ ztiles,
                                                       int nnarrow, FieldSet fs) {
   constexpr int G = NARROW_LANES, IM = NARROW_ROW_BYTES / (int)sizeof(T);
-  if (fs.n > 1) d.field = field_of(fs, (int)blockIdx.y);
+  if (d.nfields > 1) d.field = field_of(fs, (int)blockIdx.y);
   if ((int)blockIdx.x >= nnarrow) {  // a zero-row tile
     zero_row_tile<T, 1, false, false, true>(d, ztiles[blockIdx.x - nnarrow], zero_only);
     return;
@@ -1301,7 +1304,7 @@ __device__ __forceinline__ void data_gather_rows(const PlanDesc& d, const DataDe
 template <typename T, int V, int U, bool NT, int RB, int KM>
 __global__ __launch_bounds__(256) void k_apply_rows(PlanDesc d, const RowTile* __restrict__ tiles, int ntiles,
                                                     int zero_only, DataDesc dd, FieldSet fs) {
-  if (fs.n > 1) d.field = field_of(fs, (int)blockIdx.y);
+  if (d.nfields > 1) d.field = field_of(fs, (int)blockIdx.y);
   // the first dd.grid workgroups gather data rows (dispatched first, they
   // overlap the ghost-row tiles)
   if ((int)blockIdx.x < dd.grid) {
@@ -3359,7 +3362,8 @@ void device_apply(const Plan& p, void* field, void* stream, bool zero_only) {
 
 // One launch for the fields of fs (small_apply).
 static void device_apply_many(const Plan& p, const FieldSet& fs, void* stream) {
-  const PlanDesc d = make_desc(p, fs.p[0]);
+  PlanDesc d = make_desc(p, fs.p[0]);
+  d.nfields = fs.n;
   if (p.dtype == HBC_F64)
     launch_apply_t<double>(p, d, S(stream), false, fs);
   else
