@@ -579,7 +579,8 @@ __device__ __forceinline__ void rt_tile(const PlanDesc& d, const RowTile& tl, bo
 // b on every other side 10.4 us with one value per lane and a division each,
 // 7.0 in a launch of the row kernel, 6.5 so (x 32: 7.0, 3.6 and 3.9; C24 x 257
 // 3.5 in the row kernel, 3.7 so).  B: the tiles may carry b; the wide kernel
-// keeps the form without (C384 x 256 45.0 us, 45.4 with b compiled in).
+// keeps the form without, one value per lane (C384 x 256 44.2 us, with vectors
+// 44.6, with b compiled in 0.4 more).
 template <typename T, int V, bool NT, bool UA, bool B>
 __device__ __forceinline__ void zero_row_tile(const PlanDesc& d, const RowTile& t, int zero_only) {
   T* __restrict__ f = static_cast<T*>(d.field);
@@ -988,7 +989,7 @@ __global__ __launch_bounds__(256) void k_apply_wide(PlanDesc d, const WideTile* 
   WideEnt<T>* le = reinterpret_cast<WideEnt<T>*>(wide_smem + (size_t)ucap * SB);  // ecap entries
   int32_t* lp = reinterpret_cast<int32_t*>(le + ecap);                                 // WIDE_ROWS + 1 row starts
   if ((int)blockIdx.x >= nwide) {  // a zero-row tile (no barrier is reached)
-    zero_row_tile<T, (V < 16 / (int)sizeof(T) ? V : 16 / (int)sizeof(T)), NT, false, false>(d, ztiles[blockIdx.x - nwide], zero_only);
+    zero_row_tile<T, 1, false, false, false>(d, ztiles[blockIdx.x - nwide], zero_only);
     return;
   }
   // workgroups are dealt to the 8 XCDs round-robin: give each XCD a
