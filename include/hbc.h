@@ -372,8 +372,9 @@ int hbc_apply_adjoint(const hbc_plan* plan, void* grad, int64_t nelem, void* str
  * one GPU must not overlap in time (whatever their plans), and they race with
  * each other if they do.  Needs the plan's transposed tables, which the first
  * hbc_apply_adjoint or hbc_graph_create(HBC_OP_ADJOINT) builds (HBC_EINVAL
- * otherwise), and at most 2^20 counters (HBC_EINVAL beyond; hbc_apply_adjoint
- * has no such limit). */
+ * otherwise).  A plan whose kernel needs more than 2^20 counters takes the next
+ * one that needs fewer, or none; HBC_EINVAL where the last one with counters
+ * needs more too (hbc_apply_adjoint has no such limit). */
 int hbc_apply_adjoint_noalloc(const hbc_plan* plan, void* grad, int64_t nelem, void* stream);
 /* The kernels one call of `op` (HBC_OP_APPLY: hbc_apply; HBC_OP_ADJOINT:
  * hbc_apply_adjoint) launches with the plan's current launch shape, in launch
@@ -465,7 +466,7 @@ void hbc_consumer_destroy(hbc_consumer* c);
  * the ghost face's tangential index.  Device arrays of h*N and 4*h*N. */
 int hbc_cs_lagrange_weights(int64_t N, int64_t h, int32_t* base_dev, double* w_dev, void* stream);
 
-/* ---- batched persistent apply (Sec. V-C: specialise once, run many) ---------- */
+/* ---- batched apply (Sec. V-C: specialise once, run many) --------------------- */
 /* Concatenate the plans' work into one tile list (plans stay owned by the caller
  * and must outlive the batch; all plans need the same dtype and layout order). */
 int hbc_batch_create(hbc_plan* const* plans, int32_t n, hbc_batch** out);
@@ -473,7 +474,7 @@ void hbc_batch_destroy(hbc_batch* b);
 /* Bind one device field per plan (synchronous upload of the pointer table);
  * nelem[k] must equal plan k's cells * inner. */
 int hbc_batch_bind(hbc_batch* b, void* const* fields, const int64_t* nelem);
-/* One persistent launch applying every plan to its bound field. */
+/* One launch applying every plan to its bound field. */
 int hbc_batch_apply(hbc_batch* b, void* stream);
 /* Capture one hbc_batch_apply into a HIP graph (re-captured on each call), then
  * hbc_batch_graph_launch replays it.  hbc_batch_set_tune and

@@ -236,15 +236,16 @@ struct alignas(16) NarrowTile {
 // the cells src0 + (r + m) * dl, m < 4, so a run of R rows reads R + 3
 // distinct cells.  One wavefront takes a run and a slice of 64 16-byte
 // vectors of the inner values and loads each of the run's cells once.
-// rows of 256 bytes and up: the window kernel beats the row kernel from there
-// (C768 x 32 FP64: 7.4 against 8.6 us); at 128 bytes a wavefront's slice is
-// mostly idle lanes and it loses (FP32: 6.7 against 4.8 us)
+// Runs of the tuned length: rows of 256 bytes and up (C768 x 32 FP64: 7.4
+// against 8.6 us with the row kernel), with b from 512 bytes.  One run to a
+// wavefront loses below (FP32 at 128 bytes 6.7 against 4.8 us, mostly idle
+// lanes; with b C768 x 32 FP64 12.4 against 10.7): shorter rows share one, see
+// below.
 constexpr int WIN_MAXR = 16, WIN_MIN_BYTES = 256, WIN_DEFAULT_ROWS = 8;
-// segments with b: from 512 bytes (C768 x 32 FP64 with b on every strip row:
-// 12.4 us windowed at 256 bytes against 10.7 us with the row kernel)
 constexpr int WIN_MIN_BYTES_B = 512;
 // The other window-shaped rows (shorter, with b, or of a length that vectors do
-// not divide) go in runs of a fixed length, whatever the tune: 6 rows where a
+// not divide), 2 or 4 runs to a wavefront where they have at most 32 or 16
+// vectors, go in runs of a fixed length, whatever the tune: 6 rows where a
 // run is one slice, else 8.  Measured against the row kernel (C384, cold): FP64
 // x 20 5.3 against 7.6 us, x 137 15.5 against 21.8, FP32 x 33 5.2 against 6.4,
 // x 137 with b 9.4 against 11.8; C768 x 32 FP64 with b 5.4 against 7.3, FP32
@@ -360,7 +361,7 @@ constexpr int ADJW_ROW_BYTES = 128;          // plans of few entries per source:
 // x 384 16.0 and 15.5, x 512 20.0 and 20.8 (C97 h 2 20 and 25), x 1024 35 and
 // 42, x 4096 96 and 192, FP32 x 1025 57 and 72.
 constexpr int ADJW_LONG_BYTES = 8192, ADJW_COPY_BYTES = 3072;
-// tiles are kept short enough for about 3 workgroups per CU: FP64 C768 x 32
+// tiles are kept short enough for about 3 workgroups per CU: FP64 C768 h 2 x 32
 // 10.1 us with 768, 10.6 with 512, 13.9 with 1024 (two rounds of workgroups)
 constexpr int ADJW_ITEMS = 768;
 constexpr int ADJW_STAGE_BYTES = 24 * 1024;  // staged ghost slices of a tile

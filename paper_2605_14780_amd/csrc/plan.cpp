@@ -1255,7 +1255,7 @@ static int32_t cut_runs(const HostTables& T, const DevSeg& sg, int most, std::ve
 }
 
 // Sliding-window runs (see WinRun) of the segments of window rows: of at most
-// rmax rows, or WIN_FIXED_ROWS for the segments of fixed_windows.  Rows of
+// rmax rows, or of win_fixed_rows for the segments of fixed_windows.  Rows of
 // other segments keep the row tiles.
 static void build_windows(Plan& plan, int rmax) {
   HostTables& T = plan.host;
